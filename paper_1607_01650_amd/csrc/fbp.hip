@@ -135,24 +135,24 @@ __global__ __launch_bounds__(256) void k_fbp_filter(const float *__restrict__ si
 // The detector position of a tile's centre (xm, ym) at a view, in FP64: the bin
 // it falls on, the position relative to that bin, and its derivative, so that
 // the position of the pixel at (dx, dy) from the centre is off + (dx ax + dy
-// ay) / (distance over SOD) past the bin.
+// ay) / (distance from the source along the axis) past the bin.  The centre is that of the tile's part
+// of the image: a whole tile's may lie at the source, where it has no position.
 struct TilePos {
     int bin;
     float off, ax, ay;
 };
 
-__device__ __forceinline__ TilePos tile_pos(const ViewInfo &vi, double xm, double ym,
-                                            double inv_sod, double sdd_over_du, double b0)
+__device__ __forceinline__ TilePos tile_pos(const ViewInfo &vi, double xm, double ym, double sod,
+                                            double sdd_over_du, double b0)
 {
     const double ct = (double)vi.ct + (double)vi.ctl, st = (double)vi.st + (double)vi.stl;
-    const double kd = sdd_over_du * inv_sod;
-    const double m = (ym * ct - xm * st) * kd / (1.0 - (xm * ct + ym * st) * inv_sod);
+    const double m = (ym * ct - xm * st) * sdd_over_du / (sod - (xm * ct + ym * st));
     const double fl = floor(m + b0);
     TilePos o;
     o.bin = (int)fmin(fmax(fl, -1e6), 1e6);
     o.off = (float)(m + b0 - fl);
-    o.ax = (float)(m * inv_sod * ct - kd * st);
-    o.ay = (float)(m * inv_sod * st + kd * ct);
+    o.ax = (float)(m * ct - sdd_over_du * st);
+    o.ay = (float)(m * st + sdd_over_du * ct);
     return o;
 }
 
@@ -166,14 +166,17 @@ __device__ __forceinline__ float lane_f(float v, int i)
 // and view, positions relative to the tile's centre as there.  512 x 512, 360
 // views, 2048 bins of 0.85 mm: the call takes 142 us (428 us with the direct
 // filter and the positions from the isocentre).  grid (tiles, pairs) of 16 x
-// 16 pixels, XCD-ordered.
+// 16 pixels, XCD-ordered.  TILE false: positions from the isocentre, for orbits
+// so close to the image that a tile may see half the detector (the rounding of
+// a position is that of the bins it is the sum of).
+template <bool TILE>
 __global__ __launch_bounds__(256) void k_fbp_bp(const f2v *__restrict__ q,
                                                 const ViewInfo *__restrict__ views, int batch,
                                                 int nx, int ny, int V, int B, float pixel,
-                                                double inv_sod_d, double sdd_over_du, double b0,
+                                                double sod_d, double sdd_over_du, double b0,
                                                 float scale, float *__restrict__ img)
 {
-    const float inv_sod = (float)inv_sod_d;
+    const float sod = (float)sod_d;
     const unsigned item = xcd_order(block_linear(), grid_blocks());
     const int ntx = (nx + 15) / 16, nty = (ny + 15) / 16;
     const int pr = (int)(item / (unsigned)(ntx * nty));
@@ -181,10 +184,12 @@ __global__ __launch_bounds__(256) void k_fbp_bp(const f2v *__restrict__ q,
     const int x0 = (tile % ntx) * 16, y0 = (tile / ntx) * 16;
     const int c = x0 + (threadIdx.x & 15), r = y0 + (threadIdx.x >> 4);
     const int lane = threadIdx.x & 63;
-    const float xr = (c - 0.5f * (nx - 1)) * pixel * inv_sod;
-    const float yr = (r - 0.5f * (ny - 1)) * pixel * inv_sod;
-    const float dx = ((threadIdx.x & 15) - 7.5f) * pixel, dy = ((threadIdx.x >> 4) - 7.5f) * pixel;
-    const double xm = (x0 + 7.5 - 0.5 * (nx - 1)) * pixel, ym = (y0 + 7.5 - 0.5 * (ny - 1)) * pixel;
+    // the tile's part of the image: lanes past it repeat its last column and row
+    const int cl = min(c, nx - 1), rl = min(r, ny - 1);
+    const float hx = 0.5f * (min(16, nx - x0) - 1), hy = 0.5f * (min(16, ny - y0) - 1);
+    const float x = (cl - 0.5f * (nx - 1)) * pixel, y = (rl - 0.5f * (ny - 1)) * pixel;
+    const float dx = (cl - x0 - hx) * pixel, dy = (rl - y0 - hy) * pixel;
+    const double xm = (x0 + hx - 0.5 * (nx - 1)) * pixel, ym = (y0 + hy - 0.5 * (ny - 1)) * pixel;
     const int stride = B + 2 * kQPad;
     const char *base = (const char *)(q + (size_t)pr * V * stride);
     // n views from v (lane u of tp): their taps' loads first, then the sums
@@ -195,12 +200,17 @@ __global__ __launch_bounds__(256) void k_fbp_bp(const f2v *__restrict__ q,
 #pragma unroll
         for (int k = 0; k < n; ++k) {
             const ViewInfo vi = views[v + k];
-            const float inv = __builtin_amdgcn_rcpf(fmaf(-yr, vi.st, fmaf(-xr, vi.ct, 1.f)));
-            const float bf = fmaf(fmaf(dy, lane_f(tp.ay, u + k), dx * lane_f(tp.ax, u + k)), inv,
-                                  lane_f(tp.off, u + k));
+            const float inv = __builtin_amdgcn_rcpf(sod - fmaf(x, vi.ct, y * vi.st));
+            float bf;
+            if constexpr (TILE)
+                bf = fmaf(fmaf(dy, lane_f(tp.ay, u + k), dx * lane_f(tp.ax, u + k)), inv,
+                          lane_f(tp.off, u + k));
+            else
+                bf = fmaf(fmaf(-x, vi.st, y * vi.ct) * inv, (float)sdd_over_du, (float)b0);
             const float fl = floorf(bf);
             // taps h, h + 1 of the padded row; beyond the detector both are zero
-            const int h = min(max((int)fl + __builtin_amdgcn_readlane(tp.bin, u + k), -kQPad), B);
+            const int o = TILE ? __builtin_amdgcn_readlane(tp.bin, u + k) : 0;
+            const int h = min(max((int)fl + o, -kQPad), B);
             const char *rowp = base + (size_t)(v + k) * stride * 8;
             t[k] = *(const f4a8 *)(rowp + (unsigned)(h + kQPad) * 8u);
             w[k] = bf - fl;
@@ -219,7 +229,7 @@ __global__ __launch_bounds__(256) void k_fbp_bp(const f2v *__restrict__ q,
     for (int vb = 0; vb < V; vb += 64) {
         // the tile's centre at 64 views, one per lane
         const TilePos tp =
-            tile_pos(views[min(vb + lane, V - 1)], xm, ym, inv_sod_d, sdd_over_du, b0);
+            tile_pos(views[min(vb + lane, V - 1)], xm, ym, sod_d, sdd_over_du, b0);
         for (int v0 = vb; v0 < min(V, vb + 64); v0 += 8) {
             float s0 = 0.f, s1 = 0.f;
             if (v0 + 8 <= V)
@@ -259,7 +269,7 @@ constexpr size_t kBpWide = 1024;  // 16 x 16 tiles from which tiles of 32 column
 template <int TX>
 __global__ __launch_bounds__(kBpWaves * 64) void k_fbp_bp_win(
     const f2v *__restrict__ q, const ViewInfo *__restrict__ views, int batch, int nx, int ny, int V,
-    int B, float pixel, double inv_sod_d, double sdd_over_du, double b0, float scale,
+    int B, float pixel, double sod_d, double sdd_over_du, double b0, float scale,
     float *__restrict__ img)
 {
     constexpr int PX = TX / 4;  // rows of a lane; the lanes are TX columns x 64 / TX row groups
@@ -267,7 +277,7 @@ __global__ __launch_bounds__(kBpWaves * 64) void k_fbp_bp_win(
         f2v win[kBpWaves][kBpGroup][kBpWin];
         double sum[kBpWaves][PX][64];
     } sh;
-    const float inv_sod = (float)inv_sod_d;
+    const float sod = (float)sod_d;
     const unsigned item = xcd_order(block_linear(), grid_blocks());
     const int ntx = (nx + TX - 1) / TX, nty = (ny + 15) / 16;
     const int pr = (int)(item / (unsigned)(ntx * nty));
@@ -276,17 +286,20 @@ __global__ __launch_bounds__(kBpWaves * 64) void k_fbp_bp_win(
     const int lane = threadIdx.x & 63;
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int c = x0 + lane % TX, r = y0 + lane / TX * PX;
-    // a pixel's position over SOD (xr, yr), and from the tile's centre (dx, dy; exact)
-    const float x = (c - 0.5f * (nx - 1)) * pixel, y = (r - 0.5f * (ny - 1)) * pixel;
-    const float dx = (lane % TX - 0.5f * (TX - 1)) * pixel, xr = x * inv_sod;
-    float yr[PX], dy[PX];
+    // a pixel's position (x, y), and from the centre of the tile's part of the image
+    // (dx, dy; exact); lanes past that part repeat its last column and row
+    const int cl = min(c, nx - 1);
+    const float hx = 0.5f * (min(TX, nx - x0) - 1), hy = 0.5f * (min(16, ny - y0) - 1);
+    const float x = (cl - 0.5f * (nx - 1)) * pixel, dx = (cl - x0 - hx) * pixel;
+    float y[PX], dy[PX];
 #pragma unroll
     for (int i = 0; i < PX; ++i) {
-        yr[i] = (y + i * pixel) * inv_sod;
-        dy[i] = (lane / TX * PX + i - 7.5f) * pixel;
+        const int rl = min(r + i, ny - 1);
+        y[i] = (rl - 0.5f * (ny - 1)) * pixel;
+        dy[i] = (rl - y0 - hy) * pixel;
     }
-    const double xm = (x0 + 0.5 * (TX - 1) - 0.5 * (nx - 1)) * pixel;
-    const double ym = (y0 + 7.5 - 0.5 * (ny - 1)) * pixel;
+    const double xm = (x0 + hx - 0.5 * (nx - 1)) * pixel;
+    const double ym = (y0 + hy - 0.5 * (ny - 1)) * pixel;
     const int stride = B + 2 * kQPad;
     const f2v *base = q + (size_t)pr * V * stride + kQPad;
     const int v_begin = V * wid / kBpWaves, v_end = V * (wid + 1) / kBpWaves;
@@ -294,7 +307,7 @@ __global__ __launch_bounds__(kBpWaves * 64) void k_fbp_bp_win(
     double acc[PX][2] = {};
     // views v .. v + 63, one per lane; a window starts 31 bins before the tile centre's
     auto windows = [&](int v) {
-        TilePos o = tile_pos(views[min(v + lane, V - 1)], xm, ym, inv_sod_d, sdd_over_du, b0);
+        TilePos o = tile_pos(views[min(v + lane, V - 1)], xm, ym, sod_d, sdd_over_du, b0);
         o.bin -= kBpWin / 2 - 1;
         o.off += (float)(kBpWin / 2 - 1);
         return o;
@@ -324,15 +337,15 @@ __global__ __launch_bounds__(kBpWaves * 64) void k_fbp_bp_win(
         auto view = [&](int u) {
             const ViewInfo vi = views[v + u];
             const float off = lane_f(cw.off, k + u), ay = lane_f(cw.ay, k + u);
-            const float ex = fmaf(-xr, vi.ct, 1.f), px = dx * lane_f(cw.ax, k + u);
+            const float ex = fmaf(-x, vi.ct, sod), px = dx * lane_f(cw.ax, k + u);
 #pragma unroll
             for (int i0 = 0; i0 < PX; i0 += 4) {
                 f2v t0[4], t1[4];
                 float w[4], g[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    // the distance over SOD, then the position in the window (1 .. 62)
-                    const float inv = __builtin_amdgcn_rcpf(fmaf(-yr[i0 + i], vi.st, ex));
+                    // the distance, then the position in the window (1 .. 62)
+                    const float inv = __builtin_amdgcn_rcpf(fmaf(-y[i0 + i], vi.st, ex));
                     const float bf = fmaf(fmaf(dy[i0 + i], ay, px), inv, off);
                     const unsigned h = (unsigned)bf;
                     w[i] = __builtin_amdgcn_fractf(bf);
@@ -444,11 +457,11 @@ dect_status fbp(const dect_geometry *g, const float *sino, float *img, int batch
                                      std::sqrt(1.0 + rm * rm / (R * R - rm * rm))
                                : INFINITY;
     const double room = kBpWin / 2 - 2.5;
+    const float scale = (float)(2.0 * M_PI / V * R * R);  // (the weights are 1 / distance^2)
     const auto windowed = [&](auto kern, int tx) {
         hipLaunchKernelGGL(kern, dim3((g->nx + tx - 1) / tx * nty, pairs), dim3(kBpWaves * 64), 0, s,
                            (const f2v *)w->ptr, (const ViewInfo *)t->views, batch, g->nx, g->ny, V,
-                           B, (float)g->pixel_mm, 1.0 / R, D / du, b0,
-                           (float)(2.0 * M_PI / V), img);
+                           B, (float)g->pixel_mm, R, D / du, b0, scale, img);
     };
     if (std::hypot(15.5, 7.5) * grad <= room && (size_t)ntx * nty * pairs >= kBpWide) {
         windowed(k_fbp_bp_win<32>, 32);
@@ -460,9 +473,14 @@ dect_status fbp(const dect_geometry *g, const float *sino, float *img, int batch
         DECT_HIP(hipGetLastError());
         return DECT_OK;
     }
-    hipLaunchKernelGGL(k_fbp_bp, dim3(ntx * nty, pairs), dim3(256), 0, s, (const f2v *)w->ptr,
+    // bins between a tile's centre and its corners where the image comes closest to the source
+    const double rc = 0.5 * g->pixel_mm * std::hypot((double)g->nx - 1.0, (double)g->ny - 1.0);
+    const double across = std::hypot(7.5, 7.5) * g->pixel_mm * (D / (R - rc)) / du *
+                          std::sqrt(1.0 + rc * rc / (R * R - rc * rc));
+    hipLaunchKernelGGL((across < 0.5 * B ? k_fbp_bp<true> : k_fbp_bp<false>), dim3(ntx * nty, pairs),
+                       dim3(256), 0, s, (const f2v *)w->ptr,
                        (const ViewInfo *)t->views, batch, g->nx, g->ny, V, B, (float)g->pixel_mm,
-                       1.0 / R, D / du, b0, (float)(2.0 * M_PI / V), img);
+                       R, D / du, b0, scale, img);
     DECT_HIP(hipGetLastError());
     return DECT_OK;
 }

@@ -82,6 +82,24 @@ def test_fbp_fine_bins(torch):
     assert rel_l2(got, O.fbp(g, y)) <= 450 * 3 * 2.5 * 2.0 ** -24
 
 
+# Images whose last tiles lie mostly outside them: an orbit close to the image, so that such
+# a tile's own centre would be at (15.5 mm) or beyond the source, and a windowed size whose
+# tile sees as many bins as a window takes.
+@pytest.mark.parametrize("n,sod,bin_mm", [(17, 15.5, 1.3), (17, 12.1, 1.0), (33, 24.0, 1.6), (17, 60.0, 1.65)])
+def test_fbp_tiles_past_the_image(torch, n, sod, bin_mm):
+    # Positions are FP32 sums relative to the centre of the tile's part of the image: three
+    # roundings of the bins between it and its corners, times a neighbour difference of at
+    # most 2.5 of the value (white noise); the distance's rounding enters its square.
+    dect = _dect()
+    g = C.Geometry(nx=n, ny=n, pixel_mm=1.0, n_views=24, n_bins=int(1.9 * sod / bin_mm) * 2 + 1,
+                   bin_mm=bin_mm, sod_mm=sod, sdd_mm=2.0 * sod)
+    r = 0.5 * np.hypot(n - 1, n - 1)
+    bins = np.hypot(7.5, 7.5) * 2.0 * sod / (sod - r) / bin_mm / np.sqrt(1.0 - (r / sod) ** 2)
+    y = f32(P.random_sino(g, 5))
+    got = to_np(dect.fbp(to_dev(torch, y), g))
+    assert rel_l2(got, O.fbp(g, y)) <= (3 * 2.5 * max(bins, 16.0) + 4 * sod / (sod - r)) * 2.0 ** -24
+
+
 def test_fbp_pairs_equal_single_calls(torch):
     dect = _dect()
     g = RAGGED

@@ -95,10 +95,11 @@ class UnrolledADM(torch.nn.Module):
         params_of in a few launches for all steps, forward and backward (per step and
         parameter they were some 260 small ones, 0.6 ms of a 10-step training step).
         A subclass's own params_of is asked step by step."""
-        if type(self).params_of is not UnrolledADM.params_of:
+        tables = (self.log_mu, self.log_rho, self.log_xi, self.log_alpha)
+        if (type(self).params_of is not UnrolledADM.params_of
+                or any(len(t) < self.n_steps for t in tables)):  # (params_of says which row is missing)
             return [torch.stack(self.params_of(k)) for k in range(self.n_steps)]
-        logs = torch.stack((self.log_mu, self.log_rho, self.log_xi, self.log_alpha), 1)
-        return torch.exp(logs).float().unbind(0)
+        return torch.exp(torch.stack(tables, 1)).float().unbind(0)
 
     def _segment(self, g):
         def run(f, lx, ly, *params):

@@ -94,9 +94,10 @@ class UnrolledADM(torch.nn.Module):
         """(mu, rho, xi, alpha) of every step, [n_steps] rows of four: the numbers of
         params_of in a few launches for all steps, forward and backward (per step and
         parameter they were some 260 small ones, 0.6 ms of a 10-step training step).
-        A subclass's own params_of is asked step by step."""
+        A params_of that is not this class's own is asked step by step."""
         tables = (self.log_mu, self.log_rho, self.log_xi, self.log_alpha)
-        if (type(self).params_of is not UnrolledADM.params_of
+        if (getattr(self.params_of, "__func__", None) is not _own_params_of
+                or self.params_of.__self__ is not self
                 or any(len(t) < self.n_steps for t in tables)):  # (params_of says which row is missing)
             return [torch.stack(self.params_of(k)) for k in range(self.n_steps)]
         return torch.exp(torch.stack(tables, 1)).float().unbind(0)
@@ -125,3 +126,6 @@ class UnrolledADM(torch.nn.Module):
             else:
                 f, lx, ly = fn(f, lx, ly, *params)
         return f
+
+
+_own_params_of = UnrolledADM.params_of

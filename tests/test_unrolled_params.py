@@ -32,3 +32,26 @@ def test_more_steps_than_rows(rows):
     m.n_steps = 5
     with pytest.raises(IndexError):
         _run(m, rows)
+
+
+def _doubled(self, k):
+    mu, rho, xi, alpha = (torch.exp(t[k]).float() for t in (self.log_mu, self.log_rho, self.log_xi, self.log_alpha))
+    return 2 * mu, rho, xi, (k + 1) * alpha
+
+
+@pytest.mark.parametrize("where", ["instance", "other instance's", "class", "subclass"])
+def test_params_of_replaced(rows, monkeypatch, where):
+    m = U.UnrolledADM(G, n_steps=3, mu=0.5, alphas=[1e-4, 2e-4, 3e-4])
+    plain = _run(m, rows)
+    want = plain * torch.tensor([[2.0, 1.0, 1.0, k + 1.0] for k in range(3)])
+    if where == "instance":
+        m.params_of = lambda k: _doubled(m, k)
+    elif where == "other instance's":
+        other = U.UnrolledADM(G, n_steps=3, mu=1.0, alphas=[1e-4, 4e-4, 9e-4])
+        m.params_of = other.params_of
+    elif where == "class":
+        monkeypatch.setattr(U.UnrolledADM, "params_of", _doubled)
+    else:
+        sub = type("Sub", (U.UnrolledADM,), {"params_of": _doubled})
+        m = sub(G, n_steps=3, mu=0.5, alphas=[1e-4, 2e-4, 3e-4])
+    torch.testing.assert_close(_run(m, rows), want, rtol=1e-6, atol=0)

@@ -95,12 +95,15 @@ class UnrolledADM(torch.nn.Module):
         params_of in a few launches for all steps, forward and backward (per step and
         parameter they were some 260 small ones, 0.6 ms of a 10-step training step).
         A params_of that is not this class's own is asked step by step."""
-        tables = (self.log_mu, self.log_rho, self.log_xi, self.log_alpha)
-        if (getattr(self.params_of, "__func__", None) is not _own_params_of
-                or self.params_of.__self__ is not self
-                or any(len(t) < self.n_steps for t in tables)):  # (params_of says which row is missing)
-            return [torch.stack(self.params_of(k)) for k in range(self.n_steps)]
-        return torch.exp(torch.stack(tables, 1)).float().unbind(0)
+        own = self.params_of
+        if getattr(own, "__func__", None) is _own_params_of and own.__self__ is self:
+            tables = (self.log_mu, self.log_rho, self.log_xi, self.log_alpha)
+            # (of other tables, too short ones among them, params_of takes what it can)
+            if all(isinstance(t, torch.Tensor) and t.dim() == 1 and len(t) >= self.n_steps
+                   and t.dtype == tables[0].dtype for t in tables):
+                n = max(0, self.n_steps)
+                return torch.exp(torch.stack([t[:n] for t in tables], 1)).float().unbind(0)
+        return [torch.stack(own(k)) for k in range(self.n_steps)]
 
     def _segment(self, g):
         def run(f, lx, ly, *params):

@@ -55,3 +55,23 @@ def test_params_of_replaced(rows, monkeypatch, where):
         sub = type("Sub", (U.UnrolledADM,), {"params_of": _doubled})
         m = sub(G, n_steps=3, mu=0.5, alphas=[1e-4, 2e-4, 3e-4])
     torch.testing.assert_close(_run(m, rows), want, rtol=1e-6, atol=0)
+
+
+# Parameter tables that params_of takes, though they are not four float64 vectors of one length.
+@pytest.mark.parametrize("change", ["longer alphas", "float32", "list", "column", "gone"])
+def test_tables_of_other_forms(rows, change):
+    m = U.UnrolledADM(G, n_steps=3, mu=0.5, alphas=[1e-4, 2e-4, 3e-4, 4e-4, 5e-4][:5 if change == "longer alphas" else 3])
+    if change == "float32":  # each table keeps its own precision
+        m.log_rho = torch.nn.Parameter(m.log_rho.detach().float())
+    elif change == "list":
+        mu = m.log_mu.detach()
+        del m.log_mu
+        m.log_mu = torch.nn.ParameterList([torch.nn.Parameter(v.clone()) for v in mu])
+    elif change == "column":
+        m.log_xi = torch.nn.Parameter(m.log_xi.detach()[:, None][:, 0])
+    elif change == "gone":
+        rho, m.params_of = m.log_rho.detach(), None
+        del m.log_rho
+        m.params_of = lambda k: (torch.exp(m.log_mu[k]).float(), torch.exp(rho[k]).float(),
+                                 torch.exp(m.log_xi[k]).float(), torch.exp(m.log_alpha[k]).float())
+    assert torch.equal(_run(m, rows), torch.stack([torch.stack(m.params_of(k)) for k in range(3)]))

@@ -668,19 +668,23 @@ __global__ __launch_bounds__(256) void k_cone_scale_z(ConeDev g, const float *__
 // to the column's FP64 sum in LDS (read when the window arrived there).
 // Everything that does not depend on z (the exact 32.32 tap line and weight,
 // the height step, the first row) is evaluated for the rays of four views at
-// once, one ray per lane, and broadcast ray by ray (readlane where a scalar
-// operand fits, LDS where an instruction would take a second one), so control
-// flow is uniform.  The height of a row over slice z is formed relative to a
-// row and a slice near it, with the step split in two FP32 parts: rounding of
-// 1e-7 voxel, as the FP64 height of k_cone_gather has once it is an FP32
-// weight.
+// once, one ray per lane, and broadcast ray by ray through LDS (two 16-byte
+// reads; a readlane per value is VALU work), so control flow is uniform.
 //
-// Bound by VALU issue: about 27 instructions per (ray, plane) of 64 slices
-// with the window and 35 with the set-up, against 50 to 60 per voxel and view
+// The first row's height over slice z is k_cone_gather's (FP64, rounded once)
+// to a few 1e-9 voxel: the step and the height of a row near the chunk's middle
+// are split in a multiple of 2^-18 (kGGrid), whose sums below 2^6 are exact, and
+// a rest below 2^-19 as FP16 units of 2^-18.  The rows after it take the step in
+// FP32, as there.  (With both in two FP32 parts, three instructions instead of
+// four, a height loses the bits of the distance between rows: A^T's error at
+// rows 20 voxels apart was 1.5e-7, 2.8e-8 now and with k_cone_gather.)
+//
+// Bound by VALU issue: about 25 instructions per (ray, plane) of 64 slices
+// with the window and 33 with the set-up, against 50 to 60 per voxel and view
 // of k_cone_gather, which finds a column's rays and rows again for every 4
 // slices.  512 x 512 x 64, 360 x 64 x 736: 5.6 ms (18.0 ms with k_cone_gather),
 // 170 cycles per ray and SIMD; a pair on 320 x 289 x 40, 240 x 40 x 460:
-// 2.28 ms (3.94 ms).  Rays in flight (kGBatch): 2, 3, 6 and 8 take 3, 2, 19
+// 2.06 ms (3.94 ms).  Rays in flight (kGBatch): 2, 3, 6 and 8 take 3, 2, 19
 // and 21% longer than 4 (registers against latency).  Eight wavefronts per
 // SIMD instead of six are no faster.
 constexpr int kGT = 8;            // tile of columns per block side
@@ -693,8 +697,10 @@ constexpr int kGMaxRows = 8;      // rows within one voxel of a slice, at most
 constexpr int kGMinSlices = 20;
 constexpr int kGBatch = 4;         // rays whose rows are loaded together
 constexpr int kGStride = 64;      // doubles per column in LDS
+constexpr float kGGrid = 262144.f;
+constexpr double kGMaxStep = 30.0;  // voxels between rows at most, for the exact sums
 
-constexpr int kGSum = (kGT * kGT + kGT) * kGStride;  // doubles per volume in LDS
+constexpr int kGSum = kGT * kGT * kGStride;  // doubles per volume in LDS
 
 struct GatherView {
     int v;
@@ -719,23 +725,19 @@ __device__ __forceinline__ float mul_zero(float a, float b)
     return r;
 }
 
-__device__ __forceinline__ float lane_f(float v, int i)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
-}
-
 typedef float c4f __attribute__((ext_vector_type(4)));
 typedef float c3a4 __attribute__((ext_vector_type(3), aligned(4)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 
 template <int NE>
-__global__ __launch_bounds__(kGT * 64) void k_cone_gather_z(ConeDev g, GatherPlan gp,
+__global__ __launch_bounds__(kGT * 64, NE == 1 ? 6 : 4) void k_cone_gather_z(ConeDev g, GatherPlan gp,
                                                             const ConeTab *__restrict__ tab,
                                                             const float *__restrict__ yl, int zper,
                                                             float *__restrict__ vol0,
                                                             float *__restrict__ vol1)
 {
     __shared__ double sum[NE][kGSum];
-    __shared__ c4f bcast[kGT][64];
+    __shared__ c4f bcast[kGT][2][64];
     const unsigned item = xcd_order(block_linear(), grid_blocks());
     const int x0 = (int)(item % gridDim.x) * kGT;
     const int y0 = (int)(item / gridDim.x % gridDim.y) * kGT;
@@ -751,16 +753,23 @@ __global__ __launch_bounds__(kGT * 64) void k_cone_gather_z(ConeDev g, GatherPla
     const float margin = 0.02f + 1e-5f * (float)g.B;
     const double cz = (g.nz - 1) / 2.0, jc = (g.J - 1) / 2.0;
     const int slot = lane % kGSlots;
-    // column (x0 + a, y0 + b) of the tile is entry a * 8 + b of `sum`; entry 64 + wid takes
-    // what belongs to a neighbour tile's columns
+    // column (x0 + a, y0 + b) of the tile is entry a * 8 + b of `sum`
     auto phase = [&](const int cls) {
         const int cstride = (cls ? kGT : 1) * kGStride;
         double *const mine = &sum[0][(cls ? wid : wid * kGT) * kGStride + lane];
-        const int other = (kGT * kGT + wid) * kGStride - (cls ? wid : wid * kGT) * kGStride;
-        // column of a line code (16 per view): its place in LDS
-        auto column = [&](int line) {
+        // the sum of a line code's column (16 codes per view); columns of a neighbour tile
+        // have none
+        auto load = [&](int line, double (&v)[NE]) {
             const int c = line & 15;
-            return mine + (c < kGT ? c * cstride : other);
+            if (c < kGT)
+#pragma unroll
+                for (int e = 0; e < NE; ++e) v[e] = mine[c * cstride + e * kGSum];
+        };
+        auto store = [&](int line, const double (&v)[NE], const float (&add)[NE]) {
+            const int c = line & 15;
+            if (c < kGT)
+#pragma unroll
+                for (int e = 0; e < NE; ++e) mine[c * cstride + e * kGSum] = v[e] + (double)add[e];
         };
         const int pl = (cls ? y0 : x0) + wid, c0 = cls ? x0 : y0;
         const int npl = cls ? g.ny : g.nx, nq = cls ? g.nx : g.ny;
@@ -797,33 +806,39 @@ __global__ __launch_bounds__(kGT * 64) void k_cone_gather_z(ConeDev g, GatherPla
             // the line relative to the tile's, plus 16 per view of the group
             const int h = hq - c0 + (lane / kGSlots) * 16;
             const double sb = fma(t.g1, (double)pl, t.g0) * g.row;  // height step per row (> 0)
-            const float sbh = (float)sb, sbl = (float)(sb - (double)sbh);
-            const float isb = __builtin_amdgcn_rcpf(sbh);
+            const double sbg = rint(sb * kGGrid);
+            const float sbh = (float)sbg * (1.f / kGGrid), sbf = (float)sb;
+            const float isb = __builtin_amdgcn_rcpf(sbf);
             // a row near the chunk's middle; heights are taken relative to it
             const double dq0 = (cz - zc) - jc * sb;  // height of row 0 over it
             const float jm = floorf(-(float)dq0 * isb);
-            const float qc = (float)fma((double)jm, sb, dq0);
+            const double qcs = fma((double)jm, sb, dq0) * kGGrid, qcg = rint(qcs);
+            const float qc = (float)qcg * (1.f / kGGrid);
+            const h2 rest = {(_Float16)(float)(sb * kGGrid - sbg), (_Float16)(float)(qcs - qcg)};
             const float first = 1.f - (qc + 1.f) * isb;
             const unsigned row =
                 (vb * (unsigned)gp.JP + (unsigned)(gp.padlo + (ok ? (int)jm : 0))) * (4u * NE);
 
             uint64_t rem = __ballot(ok);
             if (!rem) continue;
-            if (ok) bcast[wid][lane] = c4f{first, qc, sbl, __uint_as_float(row)};
+            const uint64_t close = __ballot(sbf < 1.f), closer = __ballot(sbf < 2.f / 3.f + 1e-6f);
+            if (ok) {
+                bcast[wid][0][lane] =
+                    c4f{first, qc, __builtin_bit_cast(float, rest), __uint_as_float(row)};
+                bcast[wid][1][lane] = c4f{isb, sbh, sbf, w};
+            }
             // rays in the order of view and line, kGBatch at a time (past the last one the
             // last is repeated, and not taken): their rows are loaded together
             int pos = __builtin_amdgcn_readlane(h, __builtin_ctzll(rem));
             float cur[NE], nxt[NE];  // the window: columns pos, pos + 1 of the view
-            double s0[NE], s1[NE];   // and their sums over the views before it
+            double s0[NE] = {}, s1[NE] = {};  // and their sums over the views before it
 #pragma unroll
-            for (int e = 0; e < NE; ++e) {
-                cur[e] = nxt[e] = 0.f;
-                s0[e] = column(pos)[e * kGSum];
-                s1[e] = column(pos + 1)[e * kGSum];
-            }
+            for (int e = 0; e < NE; ++e) cur[e] = nxt[e] = 0.f;
+            load(pos, s0);
+            load(pos + 1, s1);
             while (rem) {
                 float y[kGBatch][3][NE];  // the first rows within one voxel of the slice
-                float t[kGBatch], sh[kGBatch];  // the first one's height over it, the step
+                float t[kGBatch], sf[kGBatch];  // the first one's height over it, the step
                 unsigned off[kGBatch];
                 int at[kGBatch];
                 uint64_t left = rem;
@@ -832,15 +847,24 @@ __global__ __launch_bounds__(kGT * 64) void k_cone_gather_z(ConeDev g, GatherPla
                     at[k] = left ? __builtin_ctzll(left) : at[k > 0 ? k - 1 : 0];
                     left &= left - 1;
                 }
-                c4f cst[kGBatch];
-#pragma unroll
-                for (int k = 0; k < kGBatch; ++k) cst[k] = bcast[wid][at[k]];
+                float ws[kGBatch];
+                c4f cst[kGBatch], csu[kGBatch];
 #pragma unroll
                 for (int k = 0; k < kGBatch; ++k) {
-                    sh[k] = lane_f(sbh, at[k]);
-                    const float dj = floorf(fmaf(dz, lane_f(isb, at[k]), cst[k].x));
+                    cst[k] = bcast[wid][0][at[k]];
+                    csu[k] = bcast[wid][1][at[k]];
+                }
+#pragma unroll
+                for (int k = 0; k < kGBatch; ++k) {
+                    sf[k] = csu[k].z;
+                    ws[k] = csu[k].w;
+                    const float dj = floorf(fmaf(dz, csu[k].x, cst[k].x));
                     off[k] = ((unsigned)(int)dj) * (4u * NE) + __float_as_uint(cst[k].w);
-                    t[k] = fmaf(dj, sh[k], -dz) + fmaf(dj, cst[k].z, cst[k].y);
+                    const float packed = cst[k].z;
+                    const h2 rest = __builtin_bit_cast(h2, packed);
+                    t[k] = fmaf(fmaf(dj, (float)rest.x, (float)rest.y), 1.f / kGGrid,
+                                fmaf(dj, csu[k].y, -dz) + cst[k].y);
+                    asm volatile("" : "+v"(t[k]));
                     const char *p = (const char *)yl + off[k];
                     if constexpr (NE == 1) {
                         const c3a4 r = *(const c3a4 *)p;
@@ -863,65 +887,59 @@ __global__ __launch_bounds__(kGT * 64) void k_cone_gather_z(ConeDev g, GatherPla
                     if (!rem) break;
                     rem &= rem - 1;
                     // a zero weight takes nothing, not even from a non-finite row
-                    float u[NE], tt = t[k];
-                    const float w0 = __builtin_amdgcn_fmed3f(1.f - fabsf(tt), 0.f, 1.f);
-                    tt += sh[k];
-                    const float w1 = __builtin_amdgcn_fmed3f(1.f - fabsf(tt), 0.f, 1.f);
+                    float u[NE];
+                    auto weight = [](float tt) {
+                        return __builtin_amdgcn_fmed3f(1.f - fabsf(tt), 0.f, 1.f);
+                    };
+                    const float w0 = weight(t[k]), w1 = weight(t[k] + sf[k]);
 #pragma unroll
                     for (int e = 0; e < NE; ++e)
                         u[e] = mul_zero(w0, y[k][0][e]) + mul_zero(w1, y[k][1][e]);
-                    if (__float_as_int(sh[k]) < 0x3f800000) {  // rows closer than one voxel
-                        tt += sh[k];
-                        const float w2 = __builtin_amdgcn_fmed3f(1.f - fabsf(tt), 0.f, 1.f);
+                    if (close >> at[k] & 1) {  // rows closer than one voxel
+                        const float w2 = weight(fmaf(2.f, sf[k], t[k]));
 #pragma unroll
                         for (int e = 0; e < NE; ++e) u[e] += mul_zero(w2, y[k][2][e]);
-                        if (__float_as_int(sh[k]) < 0x3f2aaaac) {  // and than 2/3
+                        if (closer >> at[k] & 1) {  // and than 2/3
                             const int rows =
-                                __builtin_amdgcn_readfirstlane((int)ceilf(2.f / sh[k]));
+                                __builtin_amdgcn_readfirstlane((int)ceilf(2.f / sf[k]));
                             for (int j = 3; j < rows; ++j) {
-                                tt += sh[k];
-                                const float wr = __builtin_amdgcn_fmed3f(1.f - fabsf(tt), 0.f, 1.f);
-                                const float *yr =
-                                    (const float *)((const char *)yl + off[k]) + j * NE;
+                                const float wr = weight(fmaf((float)j, sf[k], t[k]));
+                                const unsigned at_j = off[k] + (unsigned)j * (4u * NE);
 #pragma unroll
-                                for (int e = 0; e < NE; ++e) u[e] += mul_zero(wr, yr[e]);
+                                for (int e = 0; e < NE; ++e)
+                                    u[e] += mul_zero(wr, *(const float *)((const char *)yl + (at_j + 4u * e)));
                             }
                         }
                     }
                     const int hs = __builtin_amdgcn_readlane(h, at[k]);
-                    const float ws = lane_f(w, at[k]);
                     if (hs != pos) {  // the window moves on: its first column is complete
-                        double *const c0p = column(pos), *const c1p = column(pos + 1);
-                        double *const n0p = column(hs), *const n1p = column(hs + 1);
-                        const bool one = hs == pos + 1;
+                        store(pos, s0, cur);
+                        if (hs == pos + 1) {
 #pragma unroll
-                        for (int e = 0; e < NE; ++e) {
-                            c0p[e * kGSum] = s0[e] + (double)cur[e];
-                            if (one) {
+                            for (int e = 0; e < NE; ++e) {
                                 s0[e] = s1[e];
                                 cur[e] = nxt[e];
-                            } else {
-                                c1p[e * kGSum] = s1[e] + (double)nxt[e];
-                                s0[e] = n0p[e * kGSum];
-                                cur[e] = 0.f;
                             }
-                            s1[e] = n1p[e * kGSum];
-                            nxt[e] = 0.f;
+                        } else {
+                            store(pos + 1, s1, nxt);
+                            load(hs, s0);
+#pragma unroll
+                            for (int e = 0; e < NE; ++e) cur[e] = 0.f;
                         }
+                        load(hs + 1, s1);
+#pragma unroll
+                        for (int e = 0; e < NE; ++e) nxt[e] = 0.f;
                         pos = hs;
                     }
 #pragma unroll
                     for (int e = 0; e < NE; ++e) {
-                        cur[e] = fmaf(1.f - ws, u[e], cur[e]);
-                        nxt[e] += mul_zero(ws, u[e]);
+                        cur[e] = fmaf(1.f - ws[k], u[e], cur[e]);
+                        nxt[e] += mul_zero(ws[k], u[e]);
                     }
                 }
             }
-#pragma unroll
-            for (int e = 0; e < NE; ++e) {
-                column(pos)[e * kGSum] = s0[e] + (double)cur[e];
-                column(pos + 1)[e * kGSum] = s1[e] + (double)nxt[e];
-            }
+            store(pos, s0, cur);
+            store(pos + 1, s1, nxt);
         }
     };
 
@@ -1012,7 +1030,8 @@ dect_status cone_setup(const dect_cone_geometry *g, ConeDev &d, ConeWork *w, hip
 // hold (the gather along x then takes the call): at most kGMaxRows rows
 // within one voxel of a slice, at most kGSlots rays of a view across nine
 // lines, and a padded copy of at most about 8 times the projections and of
-// less than 4 GiB (32-bit byte offsets).  Bounds over the points within one voxel of
+// less than 4 GiB (32-bit byte offsets), and rows at most kGMaxStep voxels apart.
+// Bounds over the points within one voxel of
 // the volume: the fraction of the way from the source's plane to the panel's
 // is at least tmin there.
 bool gather_plan(const ConeDev &d, int ne, GatherPlan &gp)
@@ -1024,7 +1043,7 @@ bool gather_plan(const ConeDev &d, int ne, GatherPlan &gp)
     const double sb = d.row / d.voxel * tmin * (1.0 - 1e-6);
     const double slope = std::sqrt(1.0 + r * r / (d.sod * d.sod - r * r));
     const double margin = 0.02 + 1e-5 * d.B;
-    if (std::ceil(2.0 / sb) > kGMaxRows ||
+    if (std::ceil(2.0 / sb) > kGMaxRows || d.row / d.voxel * (d.sod + r) / d.sdd > kGMaxStep ||
         (kGT + 1) * d.voxel / (d.bin * tmin) * slope + 2.0 * margin + 1.0 > kGSlots)
         return false;
     // rows from the first one of slice 0 to the last one of slice nz - 1

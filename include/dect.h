@@ -479,9 +479,10 @@ dect_status dect_unrolled_step(int32_t nx, int32_t ny, int32_t batch, const floa
  * float32 [4]) those of (mu, rho, xi, alpha), each the FP64 sum of per-block
  * partial sums in a fixed order (bitwise reproducible).  The shrinkage is
  * differentiated where |v| > 1/rho and has zero derivative elsewhere.
- * Outputs must not overlap the inputs or each other.  Work memory (six
- * images of the batch) is library-owned per device and kept between calls
- * (or drawn from the workspace of dect_set_workspace).
+ * Outputs must not overlap the inputs or each other.  Work memory (128 KB of
+ * partial sums) is library-owned per (device, stream) and kept between calls
+ * (or drawn from the workspace of dect_set_workspace); calls on several
+ * streams may overlap.
  */
 dect_status dect_unrolled_step_backward(int32_t nx, int32_t ny, int32_t batch, const float *d_f,
                                         const float *d_lx, const float *d_ly, const float *d_hb,

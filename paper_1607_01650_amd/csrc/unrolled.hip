@@ -402,21 +402,60 @@ __global__ __launch_bounds__(256) void k_unr_bwd_prm(const double *__restrict__ 
     if (threadIdx.x == 0) gprm[blockIdx.x] = (float)tot[0];
 }
 
+// The partial sums of a backward call, kept per device and stream: calls on two
+// streams may overlap.  A buffer holds the largest grid's sums, so none grows
+// under a graph that has recorded it.
 struct UnrWork {
+    int dev;
+    hipStream_t stream;
+    bool spare;  // of no stream yet
     DevBuf part;
 };
 
 std::mutex g_unr_mu;
-std::vector<std::pair<int, std::unique_ptr<UnrWork>>> g_unr;
+std::vector<std::unique_ptr<UnrWork>> g_unr;
 
-UnrWork *unr_work()
+// The buffer of at least `bytes` for stream s.  Where an allocation must not be
+// made, in a capture that no call on this stream has prepared, it takes the
+// device's spare one, which an eager call leaves behind.
+dect_status unr_work(hipStream_t s, size_t bytes, double **part)
 {
     int dev = 0;
-    (void)hipGetDevice(&dev);
-    for (auto &p : g_unr)
-        if (p.first == dev) return p.second.get();
-    g_unr.emplace_back(dev, std::make_unique<UnrWork>());
-    return g_unr.back().second.get();
+    DECT_HIP(hipGetDevice(&dev));
+    const bool arena = caller_workspace();
+    const size_t size = arena ? bytes : (size_t)P_COUNT * kUnrGrid * 8;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool capturing =
+        !arena && (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone);
+    UnrWork *mine = nullptr, *spare = nullptr, *any = nullptr;
+    for (auto &w : g_unr) {
+        if (w->dev != dev) continue;
+        if (w->spare) spare = w.get();
+        else if (w->stream == s) mine = w.get();
+        else any = w.get();
+    }
+    if (!mine && capturing) {
+        if ((mine = spare)) {
+            mine->spare = false;
+            mine->stream = s;
+        } else if (any) {  // (all handed out: the stream's calls must not overlap its owner's)
+            mine = any;
+        }
+    }
+    auto make = [&](bool is_spare) -> UnrWork * {
+        g_unr.push_back(std::make_unique<UnrWork>());
+        UnrWork *w = g_unr.back().get();
+        w->dev = dev;
+        w->stream = s;
+        w->spare = is_spare;
+        return w;
+    };
+    if (!mine) mine = make(false);
+    dect_status st = mine->part.ensure(size);
+    if (st) return st;
+    if (!capturing && !arena && !spare && (st = make(true)->part.ensure(size))) return st;
+    *part = (double *)mine->part.ptr;
+    return DECT_OK;
 }
 
 dect_status check_img(int nx, int ny, int batch, Img &d)
@@ -521,9 +560,8 @@ dect_status unrolled_step_backward(int nx, int ny, int batch, const float *f, co
                             "dect_unrolled_step_backward: outputs overlap each other");
     const unsigned g = tile_grid(d);
     std::lock_guard<std::mutex> lk(g_unr_mu);
-    UnrWork *w = unr_work();
-    if ((st = w->part.ensure((size_t)P_COUNT * g * 8))) return st;
-    double *part = (double *)w->part.ptr;
+    double *part = nullptr;
+    if ((st = unr_work(s, (size_t)P_COUNT * g * 8, &part))) return st;
     hipLaunchKernelGGL(k_unr_bwd, dim3(g), dim3(256), 0, s, d, f, lx, ly, hb, prm, gfo, glxo, glyo, gf,
                        glx, gly, ghb, part, (size_t)g);
     DECT_HIP(hipGetLastError());

@@ -287,3 +287,52 @@ def test_unrolled_step_tile_edges(torch, B, ny, nx):
     for a, b in zip(grads[:4], rg[:4]):
         assert rel_l2(to_np(a), to_np(b)) <= 1e-5
     assert np.allclose(to_np(grads[4]), to_np(rg[4]), rtol=1e-4, atol=1e-12)
+
+
+def _step_args(torch, seed, B=4, n=256):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    a = [torch.randn((B, n, n), generator=gen, device="cuda") * s
+         for s in (1.0, 300.0, 300.0, 1000.0, 1.0, 0.01, 0.01)]
+    prm = torch.tensor([0.25, 1024.0, 256.0, 1e-4], device="cuda") * (1.0 + 0.1 * seed)
+    return (*a[:4], prm, *a[4:])
+
+
+def test_unrolled_backward_on_two_streams(torch):
+    """Overlapping backward calls of two streams keep their partial sums apart: all five
+    gradients equal the serial calls' bit for bit."""
+    from paper_1607_01650_amd import dect
+    args = [_step_args(torch, k) for k in range(2)]
+    ref = [dect.unrolled_step_backward(*a) for a in args]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    got = []
+    for _ in range(20):
+        for k in range(2):
+            with torch.cuda.stream(streams[k]):
+                got.append((k, dect.unrolled_step_backward(*args[k])))
+    torch.cuda.synchronize()
+    for k, out in got:
+        assert all(torch.equal(a, b) for a, b in zip(out, ref[k]))
+
+
+def test_unrolled_backward_captured_on_a_fresh_stream(torch):
+    """A graph recorded on streams that no eager call has used, beside eager calls."""
+    from paper_1607_01650_amd import dect
+    args = [_step_args(torch, k, 2, 100) for k in range(3)]
+    ref = [dect.unrolled_step_backward(*a) for a in args]
+    torch.cuda.synchronize()
+    graphs = []
+    for k in range(2):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+            out = dect.unrolled_step_backward(*args[k])
+        graphs.append((graph, out))
+    for _ in range(3):
+        for k, (graph, out) in enumerate(graphs):
+            for t in out:
+                t.zero_()
+            graph.replay()
+            eager = dect.unrolled_step_backward(*args[2])
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(out, ref[k]))
+            assert all(torch.equal(a, b) for a, b in zip(eager, ref[2]))

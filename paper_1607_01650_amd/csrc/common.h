@@ -179,6 +179,34 @@ void dev_free(void *p);
 // Whether a caller's workspace serves the current device's allocations.
 bool caller_workspace();
 
+// Orders the calls of several streams that share one set of device buffers: a
+// call's work waits for that of the call before it.  Under the lock that guards
+// the buffers; a call on a stream that is being captured takes no part (the
+// graph's replays are its owner's to order).
+class StreamOrder {
+  public:
+    // Over one call on stream s: waits at the start, marks the end (unless the
+    // call has waited for its own work, done()).
+    class Call {
+      public:
+        Call(StreamOrder &o, hipStream_t s);
+        ~Call();
+        dect_status status() const { return st_; }
+        void done() { done_ = true; }
+
+      private:
+        StreamOrder &o_;
+        hipStream_t s_;
+        bool captured_, done_ = false;
+        dect_status st_ = DECT_OK;
+    };
+    ~StreamOrder();
+
+  private:
+    hipEvent_t event_ = nullptr;
+    bool pending_ = false;  // event_ marks the end of a call that may still run
+};
+
 // A dry run that only counts bytes: while one is active on a thread,
 // dev_alloc returns distinct placeholder addresses that must never be
 // touched (DevBuf skips its clearing and the table upload its copies) and

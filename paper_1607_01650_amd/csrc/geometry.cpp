@@ -153,6 +153,38 @@ bool caller_workspace()
 
 DevBuf::~DevBuf() { dev_free(ptr); }
 
+// ------------------------------------------------------- StreamOrder ---
+StreamOrder::Call::Call(StreamOrder &o, hipStream_t s) : o_(o), s_(s)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    captured_ = hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+    if (captured_ || !o_.pending_) return;
+    const hipError_t e = hipStreamWaitEvent(s, o_.event_, 0);
+    if (e != hipSuccess)
+        st_ = fail(DECT_ERR_HIP, std::string("hipStreamWaitEvent failed: ") + hipGetErrorString(e));
+}
+
+StreamOrder::Call::~Call()
+{
+    if (captured_ || st_ != DECT_OK) return;
+    if (done_) {  // the call waited, and before that for the calls before it
+        o_.pending_ = false;
+        return;
+    }
+    if ((o_.event_ || hipEventCreateWithFlags(&o_.event_, hipEventDisableTiming) == hipSuccess) &&
+        hipEventRecord(o_.event_, s_) == hipSuccess) {
+        o_.pending_ = true;
+        return;
+    }
+    (void)hipStreamSynchronize(s_);  // no event to be had: the call's end is here
+    o_.pending_ = false;
+}
+
+StreamOrder::~StreamOrder()
+{
+    if (event_) (void)hipEventDestroy(event_);
+}
+
 // ---------------------------------------------------------- geometry ---
 bool GeomKey::operator==(const GeomKey &o) const
 {

@@ -623,6 +623,7 @@ __global__ __launch_bounds__(256) void k_apcg_out(const double *__restrict__ u,
 
 struct PlsWork {
     DevBuf b, res, z, p0, p1, q, minv, w, m2, pmax, prz0, prz1, prr, pbb, ppq, stat, u64;
+    StreamOrder order;
 };
 
 // Device buffers of one image-space decomposition of N pixels (nblk
@@ -774,7 +775,10 @@ dect_status pls_edge_weights(int nx, int ny, const float *x, double tau, double 
     if (!(tau >= 0.0) || !std::isfinite(tau) || !std::isfinite(eps))
         return fail(DECT_ERR_INVALID_ARG, "dect_pls_edge_weights: bad tau/eps");
     std::lock_guard<std::mutex> lk(g_pls_mu);
-    return edges_into(nx, ny, x, tau, eps, w, pls_work(), s);
+    PlsWork *W = pls_work();
+    StreamOrder::Call call(W->order, s);
+    if (call.status()) return call.status();
+    return edges_into(nx, ny, x, tau, eps, w, W, s);
 }
 
 // The image-space work buffers of N pixels in nblk reduction blocks.
@@ -906,6 +910,8 @@ dect_status pls_decompose(int nx, int ny, const float *xh, const float *xl,
     if (st) return st;
     std::lock_guard<std::mutex> lk(g_pls_mu);
     PlsWork *W = pls_work();
+    StreamOrder::Call call(W->order, s);
+    if ((st = call.status())) return st;
     const size_t N = (size_t)nx * ny;
     const int nblk = (int)((N + 256 * kPix - 1) / (256 * kPix));
     if ((st = pls_prepare(W, N, nblk))) return st;
@@ -918,8 +924,13 @@ dect_status pls_decompose(int nx, int ny, const float *xh, const float *xl,
             return st;
         w = (const float *)W->w.ptr;
     }
+    // a report waits for the call's work
+    auto finish = [&](dect_status run) {
+        if (rep && (run == DECT_OK || run == DECT_WARN_MAXITER)) call.done();
+        return run;
+    };
     if (P->mode == DECT_PLS_ATTENUATION)
-        return pls_attenuation(nx, ny, xh, xl, P, w, u1, u2, rep, W, nblk, s);
+        return finish(pls_attenuation(nx, ny, xh, xl, P, w, u1, u2, rep, W, nblk, s));
     PlsBufs B;
     B.b = (float *)W->b.ptr;
     B.res = (float *)W->res.ptr;
@@ -937,7 +948,7 @@ dect_status pls_decompose(int nx, int ny, const float *xh, const float *xl,
     B.pbb = (double *)W->pbb.ptr;
     B.ppq = (double *)W->ppq.ptr;
     B.stat = (PcgStatus *)W->stat.ptr;
-    return pcg_image_run(nx, ny, P, w, u1, u2, rep, B, s);
+    return finish(pcg_image_run(nx, ny, P, w, u1, u2, rep, B, s));
 }
 
 // ------------------------------------------------ allocation-free form ---

@@ -488,6 +488,7 @@ __global__ __launch_bounds__(256) void kp3a_out(Vol v, const double *__restrict_
 struct Pls3Work {
     DevBuf b1, b2, m2, w, res, dinv, p, q, z, part, bmax, thr, ps;
     DevBuf a_u, a_res, a_z, a_p, a_q;
+    StreamOrder order;
 };
 
 std::mutex g_pls3_mu;
@@ -542,7 +543,10 @@ dect_status pls_edge_weights3(int nx, int ny, int nz, const float *x, double tau
         return fail(DECT_ERR_INVALID_ARG, "dect_pls_edge_weights3: bad tau/eps");
     const Vol v{nx, ny, nz, (size_t)nx * ny * nz, (size_t)nx * ny};
     std::lock_guard<std::mutex> lk(g_pls3_mu);
-    return edges3_into(v, x, tau, eps, w, pls3_work(), s);
+    Pls3Work *W = pls3_work();
+    StreamOrder::Call call(W->order, s);
+    if (call.status()) return call.status();
+    return edges3_into(v, x, tau, eps, w, W, s);
 }
 
 dect_status pls_decompose3(int nx, int ny, int nz, const float *xh, const float *xl,
@@ -565,6 +569,8 @@ dect_status pls_decompose3(int nx, int ny, int nz, const float *xh, const float 
     const int nb = (int)std::min<size_t>(kMaxBlocks, (v.N + 255) / 256);
     std::lock_guard<std::mutex> lk(g_pls3_mu);
     Pls3Work *W = pls3_work();
+    StreamOrder::Call call(W->order, s);
+    if ((st = call.status())) return st;
     const bool att = p->mode == DECT_PLS_ATTENUATION;
     if ((st = W->part.ensure((size_t)R_COUNT * kMaxBlocks * 8)) ||
         (st = W->ps.ensure(sizeof(PState))))
@@ -631,6 +637,7 @@ dect_status pls_decompose3(int nx, int ny, int nz, const float *xh, const float 
         DECT_HIP(hipGetLastError());
         DECT_HIP(hipMemcpyAsync(&h, ps, sizeof(PState), hipMemcpyDeviceToHost, s));
         DECT_HIP(hipStreamSynchronize(s));
+        call.done();
         const bool capped = h.it >= p->max_iter && !(h.rn <= p->tol * h.bn);
         if (rep) {
             rep->iters = h.it;
@@ -678,6 +685,7 @@ dect_status pls_decompose3(int nx, int ny, int nz, const float *xh, const float 
         relres[m] = h.rn / h.bn;
         capped = capped || (h.it >= p->max_iter && !(h.rn <= p->tol * h.bn));
     }
+    call.done();
     if (rep) {
         rep->iters = std::max(iters[0], iters[1]);
         rep->objective = 0.0;

@@ -184,10 +184,21 @@ __global__ __launch_bounds__(256) void k_weights(const float *__restrict__ m2,
     }
 }
 
+// A launch that ends the solve says which one it is: `since` is its number plus
+// one (part A of iteration it is launch 2 it, part B 2 it + 1).  Only later
+// launches leave on it, so that every wavefront of a block decides alike, also
+// while block 0 of its own launch writes.
 struct PcgStatus {
     int32_t done, iters;
     double relres;
+    uint32_t since, pad;
 };
+
+__device__ __forceinline__ bool pcg_over(const PcgStatus *stat, unsigned launch)
+{
+    const unsigned since = stat->since;
+    return since != 0 && since <= launch;
+}
 
 // The kernels of an iteration are bound by latency at image sizes (2 MB of
 // vectors, 512 blocks): every load of a block -- the four pixels' stencils and
@@ -253,6 +264,7 @@ __global__ __launch_bounds__(256) void k_pcg_setup(
             stat[m].done = 0;
             stat[m].iters = 0;
             stat[m].relres = 0.0;
+            stat[m].since = 0;
         }
     }
 }
@@ -274,6 +286,7 @@ __device__ __forceinline__ bool pcg_begin(const double *rz_cur, const double *rz
             stat->done = 1;
             stat->iters = it;
             stat->relres = rn / bn;
+            stat->since = 2u * (unsigned)it + 1u;
         }
         return false;
     }
@@ -294,7 +307,7 @@ __global__ __launch_bounds__(256) void k_pcg_a(
     int nblk)
 {
     const int m = blockIdx.y;
-    if (stat[m].done) return;
+    if (pcg_over(stat + m, 2u * (unsigned)it)) return;
     const I N = (I)nx * (I)ny;
     const float *zm = z + (size_t)m * N, *pm = pold + (size_t)m * N;
     Pix<I> px[kPix];
@@ -344,10 +357,11 @@ __global__ __launch_bounds__(256) void k_pcg_b(
     float *__restrict__ z, const float *__restrict__ pnew, const float *__restrict__ q,
     const float *__restrict__ minv, const double *__restrict__ rz_cur,
     const double *__restrict__ p_pq, double *__restrict__ rz_next, double *__restrict__ p_rr,
-    PcgStatus *__restrict__ stat, int nx, int ny, int nblk)
+    PcgStatus *__restrict__ stat, int it, int nx, int ny, int nblk)
 {
     const int m = blockIdx.y;
-    if (stat[m].done) return;
+    const unsigned launch = 2u * (unsigned)it + 1u;
+    if (pcg_over(stat + m, launch)) return;
     const size_t N = (size_t)nx * ny;
     float *um = m == 0 ? u1 : u2;
     size_t at[kPix];
@@ -366,7 +380,10 @@ __global__ __launch_bounds__(256) void k_pcg_b(
     double sum[2];
     reduce_arrays<2>(arr, nblk, sum);
     if (!(sum[0] > 0.0)) {  // breakdown: stop with the current iterate
-        if (blockIdx.x == 0 && threadIdx.x == 0) stat[m].done = 2;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            stat[m].done = 2;
+            stat[m].since = launch + 1u;
+        }
         return;
     }
     const float a = (float)(sum[1] / sum[0]);
@@ -503,6 +520,7 @@ __global__ __launch_bounds__(256) void k_apcg_setup(
             stat[0].done = 0;
             stat[0].iters = 0;
             stat[0].relres = 0.0;
+            stat[0].since = 0;
         }
     }
 }
@@ -519,7 +537,7 @@ __global__ __launch_bounds__(256) void k_apcg_a(
     const double *__restrict__ p_rr, const double *__restrict__ p_bb, double *__restrict__ p_pq,
     PcgStatus *__restrict__ stat, int it, double tol, int nx, int ny, int nblk)
 {
-    if (stat[0].done) return;
+    if (pcg_over(stat, 2u * (unsigned)it)) return;
     const I N = (I)nx * (I)ny;
     double beta = 0.0;
     if (!pcg_begin(rz_cur, rz_prev, p_rr, p_bb, nblk, it, tol, stat, beta)) return;
@@ -563,14 +581,18 @@ __global__ __launch_bounds__(256) void k_apcg_b(
     const double *__restrict__ pnew, const double *__restrict__ q, const float *__restrict__ w,
     double gamma, AttCoef k, const double *__restrict__ rz_cur, const double *__restrict__ p_pq,
     double *__restrict__ rz_next, double *__restrict__ p_rr, PcgStatus *__restrict__ stat,
-    int nx, int ny, int nblk)
+    int it, int nx, int ny, int nblk)
 {
-    if (stat[0].done) return;
+    const unsigned launch = 2u * (unsigned)it + 1u;
+    if (pcg_over(stat, launch)) return;
     const double *const arr[2] = {p_pq, rz_cur};
     double sum[2];
     reduce_arrays<2>(arr, nblk, sum);
     if (!(sum[0] > 0.0)) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) stat[0].done = 2;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            stat[0].done = 2;
+            stat[0].since = launch + 1u;
+        }
         return;
     }
     const double a = sum[1] / sum[0];
@@ -733,7 +755,7 @@ dect_status pcg_image_run(int nx, int ny, const dect_pls_params *P, const float 
         hipLaunchKernelGGL(k_pcg_b, dim3(nblk, 2), dim3(256), 0, s, u1, u2, B.res, B.z,
                            (const float *)pnew, (const float *)B.q, (const float *)B.minv,
                            (const double *)rzb[it & 1], (const double *)B.ppq, rzb[(it + 1) & 1],
-                           B.prr, stat, nx, ny, nblk);
+                           B.prr, stat, it, nx, ny, nblk);
         DECT_HIP(hipGetLastError());
         if ((it + 1) % check_every == 0) {
             PcgStatus hs[2];
@@ -867,7 +889,7 @@ dect_status pls_attenuation(int nx, int ny, const float *xh, const float *xl,
         hipLaunchKernelGGL(part_b, dim3(nblk), dim3(256), 0, s, u, res, z, (const double *)pnew,
                            (const double *)q, w, gamma, k, (const double *)rzb[it & 1],
                            (const double *)W->ppq.ptr, rzb[(it + 1) & 1], (double *)W->prr.ptr,
-                           stat, nx, ny, nblk);
+                           stat, it, nx, ny, nblk);
         DECT_HIP(hipGetLastError());
         if ((it + 1) % check_every == 0) {
             PcgStatus hs;

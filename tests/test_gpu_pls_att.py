@@ -102,3 +102,21 @@ def test_maxiter_and_refusal(torch):
     bad = dataclasses.replace(p, mode=7)
     with pytest.raises(dect.DectError):
         dect.pls_decompose(to_dev(torch, xh), to_dev(torch, xl), bad)
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("tol", [1e-7, 0.0])
+def test_breakdown_keeps_the_iterate(torch, mode, tol):
+    # Negative pair weights make the system indefinite: <p, A p> <= 0 in the first iteration
+    # ends the solve, and every block must leave the iterate, D^-1 x, as it is.
+    dect = _dect()
+    rng = np.random.default_rng(8)
+    n = 600
+    xh, xl = 0.02 + 0.005 * rng.random((n, n)), 0.03 + 0.008 * rng.random((n, n))
+    p = dataclasses.replace(C.PlsParams(), gamma=1.0, tol=tol, mode=mode, max_iter=40)
+    w = torch.full((2, n, n), -3.0, device="cuda")
+    xs = to_dev(torch, xh), to_dev(torch, xl)
+    d1, d2, _ = dect.pls_decompose(*xs, dataclasses.replace(p, mode=0, max_iter=0), edge_w=w, report=False)
+    for _ in range(5):
+        u1, u2, rep = dect.pls_decompose(*xs, p, edge_w=w)
+        assert rep.status == 0 and torch.equal(u1, d1) and torch.equal(u2, d2)

@@ -1057,6 +1057,12 @@ bool gather_plan(const ConeDev &d, int ne, GatherPlan &gp)
     return true;
 }
 
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+}
+
 // The buffers of the gather along z, or false where they cannot be had: under a
 // caller's workspace (sized for the buffers of k_cone_gather, which are
 // smaller), out of memory, or in a capture that no call has prepared.  The
@@ -1065,11 +1071,7 @@ bool gather_buffers(const ConeDev &d, int ne, ConeWork *w, GatherPlan &gp, hipSt
 {
     if (caller_workspace()) return false;
     const size_t need = (size_t)d.V * d.B * gp.JP * 4 * ne;
-    if (w->rows.bytes < need || w->tilt.empty()) {  // not while the stream is being captured
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
-            return false;
-    }
+    if ((w->rows.bytes < need || w->tilt.empty()) && capturing(s)) return false;
     if (w->rows.bytes < need || w->views.bytes < d.V * sizeof(GatherView)) {
         if (hipStreamSynchronize(s) != hipSuccess || w->rows.ensure(need) ||
             w->views.ensure(d.V * sizeof(GatherView))) {
@@ -1126,11 +1128,21 @@ dect_status cone_project_n(const dect_cone_geometry *g, const float *const *vol,
     if (st) return st;
     const int chunks = (d.J + 63) / 64, rper = (d.J + chunks - 1) / chunks;
     const size_t copy = (size_t)(d.nx + 2 * kCPad) * (d.ny + 2 * kCPad) * (d.nz + 2 * kCPad);
-    // (a caller's workspace was sized for the two copies of k_cone_fwd and keeps them)
+    const size_t need = copy * 4 * NE;  // of k_cone_fwd_z
+    const size_t pz = d.nz + 2 * kCPad;
+    const size_t nxb = (size_t)d.nx * pz * (d.ny + 2 * kCPad) * 4;  // of k_cone_fwd, per volume
+    const size_t nyb = (size_t)d.ny * pz * (d.nx + 2 * kCPad) * 4;
     const bool by_line = NE == 1 && d.nz <= kFZSlices;
-    if (rper >= (by_line ? kFZMinRowsLine : kFZMinRows) && copy * 4 * NE < (size_t(1) << 32) && !caller_workspace()) {
+    // (a caller's workspace was sized for the two copies of k_cone_fwd and keeps them)
+    const bool can_z = need < (size_t(1) << 32) && !caller_workspace();
+    bool along_rows = can_z && rper >= (by_line ? kFZMinRowsLine : kFZMinRows);
+    const bool have_z = can_z && w->vx.bytes >= need;
+    const bool have_xy = w->vx.bytes >= nxb * NE && w->vy.bytes >= nyb * NE;
+    // a capture that a call of other rows has prepared takes that call's buffers
+    if (!(along_rows ? have_z : have_xy) && (along_rows ? have_xy : have_z) && capturing(s))
+        along_rows = !along_rows;
+    if (along_rows) {
         const size_t px = d.nx + 2 * kCPad, py = d.ny + 2 * kCPad, pzn = d.nz + 2 * kCPad;
-        const size_t need = copy * 4 * NE;
         if (w->vx.bytes < need) {
             DECT_HIP(hipStreamSynchronize(s));
             if ((st = w->vx.ensure(need))) return st;
@@ -1150,9 +1162,6 @@ dect_status cone_project_n(const dect_cone_geometry *g, const float *const *vol,
         DECT_HIP(hipGetLastError());
         return DECT_OK;
     }
-    const size_t pz = d.nz + 2 * kCPad;
-    const size_t nxb = (size_t)d.nx * pz * (d.ny + 2 * kCPad) * 4;
-    const size_t nyb = (size_t)d.ny * pz * (d.nx + 2 * kCPad) * 4;
     if (w->vx.bytes < nxb * NE || w->vy.bytes < nyb * NE) {
         DECT_HIP(hipStreamSynchronize(s));
         if ((st = w->vx.ensure(nxb * NE)) || (st = w->vy.ensure(nyb * NE))) return st;
@@ -1189,10 +1198,14 @@ dect_status cone_backproject_n(const dect_cone_geometry *g, const float *const *
     GatherPlan gp{};
     const bool along_z =
         zper >= kGMinSlices && gather_plan(d, NE, gp) && gather_buffers(d, NE, w, gp, s);
-    const size_t nray = along_z ? 0 : ntab * d.J;  // the gather along z scales into `rows`
-    if (w->yl.bytes < nray * 4 * NE || w->tab.bytes < ntab * sizeof(ConeTab)) {
+    const size_t nray = ntab * d.J;
+    // the gather along z scales into `rows`, the other into `yl`, or into `rows` too where
+    // those are there (of a call along z that prepared a capture)
+    DevBuf &scaled =
+        along_z || (w->yl.bytes < nray * 4 * NE && w->rows.bytes >= nray * 4 * NE) ? w->rows : w->yl;
+    if (scaled.bytes < nray * 4 * NE || w->tab.bytes < ntab * sizeof(ConeTab)) {
         DECT_HIP(hipStreamSynchronize(s));
-        if ((st = w->yl.ensure(nray * 4 * NE)) || (st = w->tab.ensure(ntab * sizeof(ConeTab))))
+        if ((st = scaled.ensure(nray * 4 * NE)) || (st = w->tab.ensure(ntab * sizeof(ConeTab))))
             return st;
     }
     hipLaunchKernelGGL(k_cone_tab, dim3((unsigned)((ntab + 255) / 256)), dim3(256), 0, s, d,
@@ -1213,12 +1226,12 @@ dect_status cone_backproject_n(const dect_cone_geometry *g, const float *const *
         return DECT_OK;
     }
     hipLaunchKernelGGL(k_cone_scale<NE>, dim3((unsigned)((nray + 255) / 256)), dim3(256), 0, s, d,
-                       proj[0], proj[NE - 1], (float *)w->yl.ptr);
+                       proj[0], proj[NE - 1], (float *)scaled.ptr);
     DECT_HIP(hipGetLastError());
     const int nzc = (d.nz + kZC - 1) / kZC;
     hipLaunchKernelGGL(k_cone_gather<NE>, dim3((unsigned)((d.nx + 63) / 64), (unsigned)d.ny,
                                                (unsigned)((nzc + 3) / 4)),
-                       dim3(256), 0, s, d, (const ConeTab *)w->tab.ptr, (const float *)w->yl.ptr,
+                       dim3(256), 0, s, d, (const ConeTab *)w->tab.ptr, (const float *)scaled.ptr,
                        vol[0], vol[NE - 1]);
     DECT_HIP(hipGetLastError());
     return DECT_OK;

@@ -1076,6 +1076,7 @@ bool gather_buffers(const ConeDev &d, int ne, ConeWork *w, GatherPlan &gp, hipSt
         if (hipStreamSynchronize(s) != hipSuccess || w->rows.ensure(need) ||
             w->views.ensure(d.V * sizeof(GatherView))) {
             (void)hipGetLastError();
+            set_error("");  // the call goes on without them
             return false;
         }
         w->tilt.clear();

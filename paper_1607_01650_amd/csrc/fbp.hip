@@ -168,9 +168,15 @@ __device__ __forceinline__ float lane_f(float v, int i)
 // filter and the positions from the isocentre).  grid (tiles, pairs) of 16 x
 // 16 pixels, XCD-ordered.  TILE false: positions from the isocentre, for orbits
 // so close to the image that a tile may see half the detector (the rounding of
-// a position is that of the bins it is the sum of).
-template <bool TILE>
-__global__ __launch_bounds__(256) void k_fbp_bp(const f2v *__restrict__ q,
+// a position is that of the bins it is the sum of).  A block has S wavefronts per
+// 64 pixels, with an S-th of the views each, their sums added in FP64 in order:
+// four where there are few tiles (a wavefront then waits for its taps, group by
+// group, with nothing else on its SIMD), 360 views of 4 bins per pixel: 16^2 46
+// -> 30 us, 64^2 61 -> 33, 256^2 101 -> 69; but 16 views at 384^2 26 -> 31, 360 at
+// 1024^2 745 -> 830.
+constexpr size_t kBpFew = 400;  // tiles, at most
+template <bool TILE, int S>
+__global__ __launch_bounds__(256 * S) void k_fbp_bp(const f2v *__restrict__ q,
                                                 const ViewInfo *__restrict__ views, int batch,
                                                 int nx, int ny, int V, int B, float pixel,
                                                 double sod_d, double sdd_over_du, double b0,
@@ -182,8 +188,9 @@ __global__ __launch_bounds__(256) void k_fbp_bp(const f2v *__restrict__ q,
     const int pr = (int)(item / (unsigned)(ntx * nty));
     const int tile = (int)(item % (unsigned)(ntx * nty));
     const int x0 = (tile % ntx) * 16, y0 = (tile / ntx) * 16;
-    const int c = x0 + (threadIdx.x & 15), r = y0 + (threadIdx.x >> 4);
+    const int c = x0 + (threadIdx.x & 15), r = y0 + (threadIdx.x >> 4 & 15);
     const int lane = threadIdx.x & 63;
+    const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
     // the tile's part of the image: lanes past it repeat its last column and row
     const int cl = min(c, nx - 1), rl = min(r, ny - 1);
     const float hx = 0.5f * (min(16, nx - x0) - 1), hy = 0.5f * (min(16, ny - y0) - 1);
@@ -226,19 +233,33 @@ __global__ __launch_bounds__(256) void k_fbp_bp(const f2v *__restrict__ q,
     // groups of 8 views (their loads in flight together) summed in FP32,
     // the group sums in FP64
     double acc0 = 0.0, acc1 = 0.0;
-    for (int vb = 0; vb < V; vb += 64) {
+    const int v_end = (int)((int64_t)V * (part + 1) / S);
+    for (int vb = (int)((int64_t)V * part / S); vb < v_end; vb += 64) {
         // the tile's centre at 64 views, one per lane
         const TilePos tp =
             tile_pos(views[min(vb + lane, V - 1)], xm, ym, sod_d, sdd_over_du, b0);
-        for (int v0 = vb; v0 < min(V, vb + 64); v0 += 8) {
+        for (int v0 = vb; v0 < min(v_end, vb + 64); v0 += 8) {
             float s0 = 0.f, s1 = 0.f;
-            if (v0 + 8 <= V)
+            if (v0 + 8 <= v_end)
                 group(std::integral_constant<int, 8>{}, v0, tp, v0 - vb, s0, s1);
             else
-                for (int v = v0; v < V; ++v)
+                for (int v = v0; v < v_end; ++v)
                     group(std::integral_constant<int, 1>{}, v, tp, v - vb, s0, s1);
             acc0 += (double)s0;
             acc1 += (double)s1;
+        }
+    }
+    if constexpr (S > 1) {
+        __shared__ double sum[S][2][256];
+        const int t = threadIdx.x & 255;
+        sum[part][0][t] = acc0;
+        sum[part][1][t] = acc1;
+        __syncthreads();
+        if (part > 0) return;
+#pragma unroll
+        for (int k = 1; k < S; ++k) {
+            acc0 += sum[k][0][t];
+            acc1 += sum[k][1][t];
         }
     }
     if (c >= nx || r >= ny) return;
@@ -477,8 +498,10 @@ dect_status fbp(const dect_geometry *g, const float *sino, float *img, int batch
     const double rc = 0.5 * g->pixel_mm * std::hypot((double)g->nx - 1.0, (double)g->ny - 1.0);
     const double across = std::hypot(7.5, 7.5) * g->pixel_mm * (D / (R - rc)) / du *
                           std::sqrt(1.0 + rc * rc / (R * R - rc * rc));
-    hipLaunchKernelGGL((across < 0.5 * B ? k_fbp_bp<true> : k_fbp_bp<false>), dim3(ntx * nty, pairs),
-                       dim3(256), 0, s, (const f2v *)w->ptr,
+    const bool rel = across < 0.5 * B, few = (size_t)ntx * nty * pairs <= kBpFew;
+    const auto bp = few ? (rel ? k_fbp_bp<true, 4> : k_fbp_bp<false, 4>)
+                        : (rel ? k_fbp_bp<true, 1> : k_fbp_bp<false, 1>);
+    hipLaunchKernelGGL(bp, dim3(ntx * nty, pairs), dim3(few ? 1024 : 256), 0, s, (const f2v *)w->ptr,
                        (const ViewInfo *)t->views, batch, g->nx, g->ny, V, B, (float)g->pixel_mm,
                        R, D / du, b0, scale, img);
     DECT_HIP(hipGetLastError());

@@ -100,6 +100,21 @@ def test_fbp_tiles_past_the_image(torch, n, sod, bin_mm):
     assert rel_l2(got, O.fbp(g, y)) <= (3 * 2.5 * max(bins, 16.0) + 4 * sod / (sod - r)) * 2.0 ** -24
 
 
+# The general kernel's split over the views (a quarter of them per wavefront up to 400 tiles):
+# fewer views than parts, remainders of parts, groups and chunks, both sides of the line.
+@pytest.mark.parametrize("n,views", [(17, 1), (17, 3), (17, 4), (17, 5), (33, 35), (33, 67), (17, 261), (321, 10),
+                                     (320, 10)])
+def test_fbp_general_parts(torch, n, views):
+    # White noise; a position is the sum of at most 60 bins within a tile and the tile's FP64
+    # position: three roundings of 2^-24 of that, times a neighbour difference of at most 2.5
+    # of the value, rms below half of it: 60 * 3 * 2.5 * 2^-25
+    dect = _dect()
+    g = C.Geometry(nx=n, ny=n, pixel_mm=1.0, n_views=views, n_bins=6 * n, bin_mm=0.4, sod_mm=4.0 * n, sdd_mm=8.0 * n)
+    y = f32(P.random_sino(g, 6))
+    got = to_np(dect.fbp(to_dev(torch, y), g))
+    assert rel_l2(got, O.fbp(g, y)) <= 60 * 3 * 2.5 * 2.0 ** -25
+
+
 def test_fbp_pairs_equal_single_calls(torch):
     dect = _dect()
     g = RAGGED

@@ -601,7 +601,8 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(const u16 *__restrict__ dZ,
                                                const u16 *__restrict__ X,
                                                float *__restrict__ part, int H, int W, int Cin,
                                                int Cout, int nstrip, int nstrip_n, int nrc, int kst,
-                                               int nsn, int nsplit, size_t len, size_t pstride)
+                                               int nsn, int nsplit, int by_xcd, size_t len,
+                                               size_t pstride)
 {
     constexpr int T = KS * KS, XR = wg_xrows(KS), ZC = 16 * TMS, XC = 16 * TNS * WN;
     constexpr int WR = 4 / WN;
@@ -610,9 +611,10 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(const u16 *__restrict__ dZ,
     extern __shared__ __align__(16) unsigned char lds_raw[];
     u16 *sZ = (u16 *)lds_raw;           // [4][ZC][kWgLD]
     u16 *sX = sZ + 4 * ZC * kWgLD;      // [XR][XC][kWgLD]: element k is column c0 - halo + k
-    // the splits of a chunk, which read the same rows, eight blocks apart: on
-    // one XCD (consecutive blocks go to different ones), whose L2 they share
-    const int bq = blockIdx.x >> 3, split = bq % nsplit, chunk = bq / nsplit * 8 + (blockIdx.x & 7);
+    // by_xcd: the splits of a chunk, which read the same rows, eight blocks apart:
+    // on one XCD (consecutive blocks go to different ones), whose L2 they share
+    const int bq = by_xcd ? blockIdx.x >> 3 : blockIdx.x, split = bq % nsplit;
+    const int chunk = by_xcd ? bq / nsplit * 8 + (blockIdx.x & 7) : bq / nsplit;
     if (chunk >= nstrip_n * nrc) return;
     const int sm = split / nsn, sn = split - sm * nsn;
     const int rc = chunk % nrc, strip = chunk / nrc;
@@ -1354,22 +1356,23 @@ dect_status dect_nn_conv_fwd_masked(const void *x, const void *w, const float *b
 // counts.  For 3x3 one input tile per wave, as many waves apart as divide the
 // layer's: four (64 -> 32 at 8 x 512^2) read dZ once and take 112 us, one took
 // 264.  (3, 1, 4) spills its registers.
+//
+// On small planes the partial sums' bytes allow few chunks, and the first entry
+// may leave most of the chip idle: the first that gives enough blocks is taken,
+// or the one that gives most.  Below kWgXcdChunks chunks the blocks go to the XCDs
+// as they come (a chunk's splits on one XCD, fewer than eight chunks use as many
+// XCDs), and narrower tiles pay longer.  Event times with the partial sums (us),
+// with a wave per row and one input tile / the first entry, by XCD / this: 4 x 32^2
+// 128 -> 128 24 / 36 / 21, 16^2 64 -> 64 16 / 21 / 14, 300 x 3 128 -> 64 97 / 224 / 96;
+// both sides of the lines: 4 x 64^2 128 -> 128 (16 chunks) 128 blocks 27.9, 256
+// 24.6, 512 27.2; 8 x 32^2 256 -> 128 (8 chunks) 128 blocks 38.5, 256 31.4, 512 29.7, 1024
+// 33.6; 8 chunks by XCD 25.5, as they come 24.8, 16 chunks 20.6 and 21.2.
+constexpr size_t kWgEnough = 200, kWgEnoughFew = 500;
+constexpr int kWgXcdChunks = 16;
+
 struct WgTiles {
     int tms, tns, wn;
 };
-
-static WgTiles wgrad_tiles(int ks, int TM, int TN)
-{
-    static const WgTiles k3[] = {{2, 1, 4}, {2, 1, 2}, {3, 1, 2}, {1, 1, 4}, {1, 1, 2},
-                                 {2, 1, 1}, {3, 1, 1}, {1, 2, 1}, {1, 1, 1}};
-    static const WgTiles k1[] = {{4, 2, 1}, {3, 3, 1}, {2, 3, 1}, {3, 2, 1}, {4, 1, 1}, {2, 2, 1},
-                                 {3, 1, 1}, {1, 3, 1}, {2, 1, 1}, {1, 2, 1}, {1, 1, 1}};
-    const WgTiles *list = ks == 3 ? k3 : k1;
-    const int n = ks == 3 ? 9 : 11;
-    for (int i = 0; i < n; ++i)
-        if (TM % list[i].tms == 0 && TN % (list[i].tns * list[i].wn) == 0) return list[i];
-    return {1, 1, 1};
-}
 
 #define WG_KERNELS(WG)                                                                          \
     WG(3, 2, 1, 4) WG(3, 1, 1, 4) WG(3, 2, 1, 2) WG(3, 3, 1, 2) WG(3, 1, 1, 2) WG(3, 2, 1, 1)   \
@@ -1378,7 +1381,7 @@ static WgTiles wgrad_tiles(int ks, int TM, int TN)
     WG(1, 3, 1, 1) WG(1, 1, 3, 1) WG(1, 2, 1, 1) WG(1, 1, 2, 1) WG(1, 1, 1, 1)
 
 using WgKernel = void (*)(const u16 *, const u16 *, float *, int, int, int, int, int, int, int, int,
-                          int, int, size_t, size_t);
+                          int, int, int, size_t, size_t);
 
 static WgKernel wgrad_kernel(int ks, const WgTiles &t)
 {
@@ -1391,15 +1394,14 @@ static WgKernel wgrad_kernel(int ks, const WgTiles &t)
 
 struct WgradPlan {
     WgKernel kernel;
-    int nsm, nsn, nstrip, nrc, kst, nchunk, nseg;
+    int nsm, nsn, nstrip, nrc, kst, nchunk, nseg, by_xcd;
     size_t lds, len, pstride;
 };
 
-static WgradPlan wgrad_plan(int N, int H, int W, int Cin, int Cout, int ksize)
+static WgradPlan wgrad_plan_of(const WgTiles &t, int N, int H, int W, int Cin, int Cout, int ksize)
 {
     WgradPlan q;
     const int CoutP = (Cout + 15) / 16 * 16, CinP = (Cin + 15) / 16 * 16;
-    const WgTiles t = wgrad_tiles(ksize, CoutP / 16, CinP / 16);
     q.kernel = wgrad_kernel(ksize, t);
     q.nsm = CoutP / 16 / t.tms;
     q.nsn = CinP / 16 / (t.tns * t.wn);
@@ -1415,8 +1417,10 @@ static WgradPlan wgrad_plan(int N, int H, int W, int Cin, int Cout, int ksize)
     q.lds = std::max(stage, red);
     // one round of resident blocks, fewer while the partials would outweigh
     // twice the layer's own bytes
-    const size_t target = (size_t)resident_blocks((const void *)q.kernel, q.lds);
-    size_t kst = std::max<size_t>(1, (strips * RG * nsplit + target - 1) / target);
+    const size_t units = strips * RG * nsplit;
+    const size_t target =
+        units <= kWgEnough ? kWgEnough : (size_t)resident_blocks((const void *)q.kernel, q.lds);
+    size_t kst = std::max<size_t>(1, (units + target - 1) / target);
     const double in_bytes = (double)N * H * W * (Cin + Cout) * 2;
     while (kst < RG && (double)strips * ((RG + kst - 1) / kst) * q.pstride * 4 > 2.0 * in_bytes)
         kst *= 2;
@@ -1425,7 +1429,36 @@ static WgradPlan wgrad_plan(int N, int H, int W, int Cin, int Cout, int ksize)
     q.nrc = (int)((RG + kst - 1) / kst);
     q.nchunk = (int)(strips * q.nrc);
     q.nseg = sum_segments(q.nchunk, q.pstride);
+    q.by_xcd = q.nchunk >= kWgXcdChunks;
     return q;
+}
+
+static WgradPlan wgrad_plan(int N, int H, int W, int Cin, int Cout, int ksize)
+{
+    static const WgTiles k3[] = {{2, 1, 4}, {2, 1, 2}, {3, 1, 2}, {1, 1, 4}, {1, 1, 2},
+                                 {2, 1, 1}, {3, 1, 1}, {1, 2, 1}, {1, 1, 1}};
+    static const WgTiles k1[] = {{4, 2, 1}, {3, 3, 1}, {2, 3, 1}, {3, 2, 1}, {4, 1, 1}, {2, 2, 1},
+                                 {3, 1, 1}, {1, 3, 1}, {2, 1, 1}, {1, 2, 1}, {1, 1, 1}};
+    const WgTiles *list = ksize == 3 ? k3 : k1;
+    const int n = ksize == 3 ? 9 : 11, TM = (Cout + 15) / 16, TN = (Cin + 15) / 16;
+    WgradPlan best{};
+    size_t most = 0;
+    for (int i = 0; i < n; ++i) {
+        if (TM % list[i].tms != 0 || TN % (list[i].tns * list[i].wn) != 0) continue;
+        const WgradPlan q = wgrad_plan_of(list[i], N, H, W, Cin, Cout, ksize);
+        const size_t blocks = (size_t)q.nchunk * q.nsm * q.nsn;
+        if (blocks > most) {
+            most = blocks;
+            best = q;
+        }
+        if (most >= (q.by_xcd ? kWgEnough : kWgEnoughFew) || ksize == 1) break;
+    }
+    return best;
+}
+
+static size_t wgrad_bytes(const WgradPlan &q)
+{
+    return ((size_t)q.nchunk + q.nseg) * q.pstride * sizeof(float);
 }
 
 size_t dect_nn_wgrad_workspace(int32_t N, int32_t H, int32_t W, int32_t Cin, int32_t Cout,
@@ -1433,8 +1466,7 @@ size_t dect_nn_wgrad_workspace(int32_t N, int32_t H, int32_t W, int32_t Cin, int
 {
     if (N <= 0 || H <= 0 || W <= 0 || Cin <= 0 || Cout <= 0 || (ksize != 1 && ksize != 3))
         return 0;
-    const WgradPlan q = wgrad_plan(N, H, W, Cin, Cout, ksize);
-    return ((size_t)q.nchunk + q.nseg) * q.pstride * sizeof(float);
+    return wgrad_bytes(wgrad_plan(N, H, W, Cin, Cout, ksize));
 }
 
 dect_status dect_nn_conv_wgrad(const void *dz, const void *x, float *dw, float *db, int32_t N,
@@ -1446,10 +1478,10 @@ dect_status dect_nn_conv_wgrad(const void *dz, const void *x, float *dw, float *
     if (Cin <= 0 || Cout <= 0 || Cin % 8 != 0 || Cout % 8 != 0 || Cin > 256 || Cout > 256 ||
         (ksize != 1 && ksize != 3))
         return nn_fail(DECT_ERR_INVALID_ARG, "conv_wgrad: Cin, Cout % 8 and <= 256");
-    if (ws_bytes < dect_nn_wgrad_workspace(N, H, W, Cin, Cout, ksize))
-        return nn_fail(DECT_ERR_INVALID_ARG, "conv_wgrad: workspace too small");
     const WgradPlan q = wgrad_plan(N, H, W, Cin, Cout, ksize);
-    const size_t nblk = ((size_t)q.nchunk + 7) / 8 * 8 * q.nsm * q.nsn;
+    if (ws_bytes < wgrad_bytes(q))
+        return nn_fail(DECT_ERR_INVALID_ARG, "conv_wgrad: workspace too small");
+    const size_t nblk = (q.by_xcd ? ((size_t)q.nchunk + 7) / 8 * 8 : q.nchunk) * q.nsm * q.nsn;
     if (nblk > 0x7fffffffu) return nn_fail(DECT_ERR_INVALID_ARG, "conv_wgrad: problem too large");
     float *part = (float *)workspace;
     float *seg = part + (size_t)q.nchunk * q.pstride;
@@ -1457,7 +1489,7 @@ dect_status dect_nn_conv_wgrad(const void *dz, const void *x, float *dw, float *
     if (!q.kernel) return nn_fail(DECT_ERR_INVALID_ARG, "conv_wgrad: no kernel for this tiling");
     hipLaunchKernelGGL(q.kernel, dim3((unsigned)nblk), dim3(256), (unsigned)q.lds, s, (const u16 *)dz,
                        (const u16 *)x, part, H, W, Cin, Cout, q.nstrip, N * q.nstrip, q.nrc, q.kst, q.nsn,
-                       q.nsm * q.nsn, q.len, q.pstride);
+                       q.nsm * q.nsn, q.by_xcd, q.len, q.pstride);
     NN_HIP(hipGetLastError());
     const int L = (q.nchunk + q.nseg - 1) / q.nseg;
     hipLaunchKernelGGL(k_sum_seg, dim3(blocks(q.pstride), q.nseg), dim3(256), 0, s, part, seg,

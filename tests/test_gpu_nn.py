@@ -143,6 +143,26 @@ def test_wgrad_splits(torch, case):
     assert rel_l2(_np(gb), rb) <= 1e-5
 
 
+@pytest.mark.parametrize("case", [(1, 8, 8, 96, 48), (1, 16, 16, 64, 64), (4, 32, 32, 128, 128), (1, 300, 3, 64, 64),
+                                  (8, 32, 32, 256, 128), (1, 5, 7, 16, 16), (4, 64, 64, 96, 96), (2, 40, 65, 128, 96)],
+                         ids=str)
+def test_wgrad_small_planes(torch, case):
+    """3x3 weight gradients of planes with few chunks, where narrower tiles and
+    the plain block order are taken: exact products of bfloat16 values in FP32
+    sums, as in test_wgrad_splits."""
+    nn = _nn()
+    N, H, W, Ci, Co = case
+    rng = np.random.default_rng(9)
+    x = R.bf16(rng.standard_normal((N, H, W, Ci)))
+    dz = R.bf16(rng.standard_normal((N, H, W, Co)))
+    gw = torch.zeros((9, Co, Ci), device="cuda")
+    gb = torch.zeros((Co,), device="cuda")
+    nn.conv_wgrad(_bf(torch, dz), _bf(torch, x), Co, 3, gw, gb)
+    rw, rb = R.conv_dw(dz, x, 3, Co)
+    assert rel_l2(_np(gw), rw) <= 1e-5
+    assert rel_l2(_np(gb), rb) <= 1e-5
+
+
 def test_pool_shuffle_concat_exact(torch):
     nn = _nn()
     rng = np.random.default_rng(3)

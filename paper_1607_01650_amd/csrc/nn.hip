@@ -341,6 +341,27 @@ constexpr size_t conv3_lds(int nt, int nch, bool wall, int out_f32)
 }
 static_assert(conv3_lds(8, 1, false, 1) <= kC3LdsMax, "the 3x3 kernel's LDS must fit a CU");
 
+// Window pixel (row hr, column hc) of a thread's items, 64 pixels apart.
+struct WinPx {
+    int hr, hc;
+    __device__ __forceinline__ explicit WinPx(int tid)
+    {
+        const int px = tid >> 2;  // below 64: in the first two rows
+        hr = px >= kC3HC;
+        hc = px - hr * kC3HC;
+    }
+    __device__ __forceinline__ void next()
+    {
+        hr += 1;
+        hc += 64 - kC3HC;
+        if (hc >= kC3HC) {
+            hr += 1;
+            hc -= kC3HC;
+        }
+    }
+};
+static_assert(kC3HC <= 64 && 64 < 2 * kC3HC, "64 pixels on: one or two rows");
+
 // Byte offset of the 16-byte piece c (0..3) of a staged 64-byte row: pieces
 // are rotated by col, the row's window column or output channel, so that a
 // fragment read (16 neighbouring rows, one piece each) touches every bank once
@@ -406,11 +427,11 @@ __global__ __launch_bounds__(256, NT <= 4 ? 2 : 1) void k_conv3(
         // may point before the image: only pixels inside it are dereferenced
         const u16 *Xt = X + (((long long)n * H + r0 - 1) * W + c0 - 1) * Cin + c * kC3Chunk;
         w.ok = 0;
+        WinPx at(tid);
+        const int ci = (tid & 3) * 8;
 #pragma unroll
-        for (int k = 0; k < KW; ++k) {
-            const int it = tid + 256 * k;
-            const int px = it >> 2, ci = (it & 3) * 8;
-            const int hr = px / kC3HC, hc = px % kC3HC;
+        for (int k = 0; k < KW; ++k, at.next()) {
+            const int it = tid + 256 * k, hr = at.hr, hc = at.hc;
             const bool in = (256 * k + 256 <= NWIN || it < NWIN) &
                             ((unsigned)(r0 - 1 + hr) < (unsigned)H) &
                             ((unsigned)(c0 - 1 + hc) < (unsigned)W) & (c * kC3Chunk + ci < Cin);
@@ -419,23 +440,27 @@ __global__ __launch_bounds__(256, NT <= 4 ? 2 : 1) void k_conv3(
             w.v[k] = *(const uint4 *)(in ? p : X);
         }
     };
+    // item k of a thread lies 64 rows after item 0, in global memory and in LDS
     auto weights = [&](int c, unsigned char *dst) {
         const int tid = opaque_tid();
+        const int row = tid >> 2, ci = c * kC3Chunk + (tid & 3) * 8;
+        const bool in = ci < Cin;
+        const u16 *src = Wk + (in ? row * Cin + ci : 0);
+        dst += c3_at(row, row, tid & 3);
 #pragma unroll
         for (int g = 0; g < KB; g += 8) {
             uint4 v[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                const int it = tid + 256 * (g + k), ci = c * kC3Chunk + (it & 3) * 8;
+                const bool all = 256 * (g + k) + 256 <= NWTS;
                 if (g + k < KB)
-                    v[k] = *(const uint4 *)(Wk + (((it < NWTS) & (ci < Cin)) ? (it >> 2) * Cin + ci : 0));
+                    v[k] = *(const uint4 *)(all || tid + 256 * (g + k) < NWTS ? src + 64 * (g + k) * Cin : Wk);
             }
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                const int it = tid + 256 * (g + k), ci = c * kC3Chunk + (it & 3) * 8;
-                if (g + k < KB && (256 * (g + k) + 256 <= NWTS || it < NWTS))
-                    *(uint4 *)(dst + c3_at(it >> 2, it >> 2, it & 3)) =
-                        ci < Cin ? v[k] : make_uint4(0, 0, 0, 0);
+                const bool all = 256 * (g + k) + 256 <= NWTS;
+                if (g + k < KB && (all || tid + 256 * (g + k) < NWTS))
+                    *(uint4 *)(dst + 64 * 64 * (g + k)) = in ? v[k] : make_uint4(0, 0, 0, 0);
             }
         }
     };
@@ -451,12 +476,12 @@ __global__ __launch_bounds__(256, NT <= 4 ? 2 : 1) void k_conv3(
         __syncthreads();  // the chunk or tile before is done with the LDS
         {
             const int tid = opaque_tid();
+            WinPx at(tid);
 #pragma unroll
-            for (int k = 0; k < KW; ++k) {
-                const int it = tid + 256 * k;
+            for (int k = 0; k < KW; ++k, at.next()) {
                 const unsigned keep = 0u - (w.ok >> k & 1u);
                 const uint4 v = w.v[k];
-                *(uint4 *)(win + c3_at(it >> 2, (it >> 2) % kC3HC, it & 3)) =
+                *(uint4 *)(win + c3_at((tid >> 2) + 64 * k, at.hc, tid & 3)) =
                     make_uint4(v.x & keep, v.y & keep, v.z & keep, v.w & keep);
             }
         }

@@ -76,7 +76,9 @@ __global__ __launch_bounds__(256) void kb_tv(const SliceDev *__restrict__ S,
         const int4 w = items[it];
         const SliceDev &d = S[w.x];
         const int e = w.y;
-        {
+        // (before the tile's loads here: 14 of 16 slices stopped, 20 iterations 4.01 -> 3.52 ms;
+        // none stopped, the same)
+        if (!d.P.sc[e].stopped && !d.P.sc[e].stop_next) {
             const int gx = (d.nx + kTX - 1) / kTX, gy = (d.ny + kTY - 1) / kTY;
             const size_t blk = (size_t)e * gx * gy + (size_t)w.z * gx + w.w;
             AdmImg m = img_of(d, e, par);

@@ -33,6 +33,7 @@
 #include <mutex>
 #include <vector>
 
+#include "reduce.h"
 #include "volume.h"
 #include "xcd.h"
 
@@ -293,15 +294,6 @@ constexpr int kFZMinRows = 32, kFZMinRowsLine = 24;
 template <int NE> struct ZPair;
 template <> struct ZPair<1> { typedef float T __attribute__((ext_vector_type(2), aligned(4))); };
 template <> struct ZPair<2> { typedef float T __attribute__((ext_vector_type(4), aligned(8))); };
-
-// Orders a wavefront's LDS accesses before and after it (the hardware takes
-// them in order; no instruction).
-__device__ __forceinline__ void wave_order()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 constexpr int kFZSlices = 64;  // slices at most with LINE (one per lane)
 constexpr int kFZUnroll = 4;   // planes per FP32 sum, and whose lines are in flight together
@@ -822,11 +814,13 @@ __global__ __launch_bounds__(kGT * 64, NE == 1 ? 6 : 4) void k_cone_gather_z(Con
             uint64_t rem = __ballot(ok);
             if (!rem) continue;
             const uint64_t close = __ballot(sbf < 1.f), closer = __ballot(sbf < 2.f / 3.f + 1e-6f);
+            wave_order();  // the rays of the views before have been read
             if (ok) {
                 bcast[wid][0][lane] =
                     c4f{first, qc, __builtin_bit_cast(float, rest), __uint_as_float(row)};
                 bcast[wid][1][lane] = c4f{isb, sbh, sbf, w};
             }
+            wave_order();
             // rays in the order of view and line, kGBatch at a time (past the last one the
             // last is repeated, and not taken): their rows are loaded together
             int pos = __builtin_amdgcn_readlane(h, __builtin_ctzll(rem));

@@ -1,9 +1,19 @@
-// FP64 sums over a wavefront and a block in a fixed order, by VALU lane moves.
+// FP64 sums over a wavefront and a block in a fixed order, by VALU lane moves;
+// the order of a wavefront's own LDS accesses.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 namespace dect {
+
+// Orders a wavefront's LDS accesses before and after it (the hardware takes
+// them in order; no instruction).
+__device__ __forceinline__ void wave_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // v of this lane moved along the wavefront by the DPP control CTRL (rows of 16
 // lanes not in ROW_MASK, and lanes whose source lies outside their row, get

@@ -20,6 +20,7 @@
 
 #include "common.h"
 #include "proj_device.h"
+#include "reduce.h"
 #include "xcd.h"
 
 namespace dect {
@@ -347,8 +348,10 @@ __global__ __launch_bounds__(kBpWaves * 64) void k_fbp_bp_win(
     TilePos cw = nw;  // of the group being walked: lanes k ..
     for (int v = v_begin; v < v_end; v += kBpGroup) {
         const int k = (v - v_begin) & 63, kn = (k + kBpGroup) & 63;
+        wave_order();  // the group before has been read
 #pragma unroll
         for (int u = 0; u < kBpGroup; ++u) win[u][lane] = pre[u];
+        wave_order();
         if (k == 0) cw = nw;
         if (v + kBpGroup < v_end) {
             if (kn == 0) nw = windows(v + kBpGroup);

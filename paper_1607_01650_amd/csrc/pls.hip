@@ -40,12 +40,16 @@ __device__ __forceinline__ void reduce_arrays(const double *const (&a)[NV], int 
 
 // A thread's pixel j of kPix (stride 256): its index, clamped to the last
 // pixel, the indices of its four neighbours (its own where there is none) and
-// which of them exist.  I: an unsigned type that holds N.
+// which of them exist.  I: an unsigned type that holds the launch's last index, up
+// to kPix * 256 - 1 past N (small_index).
 template <typename I>
 struct Pix {
     I i, r, l, d, u;
     bool in, hr, hl, hd, hu;
 };
+
+constexpr bool small_index(size_t N) { return N <= 0x100000000ull - 256 * kPix; }
+static_assert(small_index(0xFFFFFC00u) && !small_index(0xFFFFFC01u), "the last block's indices fit 32 bits");
 
 template <typename I>
 __device__ __forceinline__ Pix<I> pixel_at(int j, int nx, int ny, I N)
@@ -736,7 +740,7 @@ dect_status pcg_image_run(int nx, int ny, const dect_pls_params *P, const float 
     float *pbuf[2] = {B.p0, B.p1};
     double *rzb[2] = {B.prz0, B.prz1};
     // 32-bit pixel indices where the image allows them
-    const bool small = N <= 0xFFFFFFFFu;
+    const bool small = small_index(N);
     const auto setup = small ? k_pcg_setup<unsigned> : k_pcg_setup<size_t>;
     const auto part_a = small ? k_pcg_a<unsigned> : k_pcg_a<size_t>;
     hipLaunchKernelGGL(setup, dim3(nblk, 2), dim3(256), 0, s, (const float *)B.b, w, gamma,
@@ -867,7 +871,7 @@ dect_status pls_attenuation(int nx, int ny, const float *xh, const float *xl,
     double *q = (double *)W->q.ptr;
     double *pbuf[2] = {(double *)W->p0.ptr, (double *)W->p1.ptr};
     double *rzb[2] = {(double *)W->prz0.ptr, (double *)W->prz1.ptr};
-    const bool small = N <= 0xFFFFFFFFu;  // 32-bit pixel indices where the image allows them
+    const bool small = small_index(N);  // 32-bit pixel indices where the image allows them
     const auto setup = small ? k_apcg_setup<unsigned> : k_apcg_setup<size_t>;
     const auto part_a = small ? k_apcg_a<unsigned> : k_apcg_a<size_t>;
     const auto part_b = small ? k_apcg_b<unsigned> : k_apcg_b<size_t>;

@@ -1401,7 +1401,7 @@ struct WgTiles {
 
 #define WG_KERNELS(WG)                                                                          \
     WG(3, 2, 1, 4) WG(3, 1, 1, 4) WG(3, 2, 1, 2) WG(3, 3, 1, 2) WG(3, 1, 1, 2) WG(3, 2, 1, 1)   \
-    WG(3, 3, 1, 1) WG(3, 1, 2, 1) WG(3, 1, 1, 1)                                 \
+    WG(3, 3, 1, 1) WG(3, 1, 1, 1)                                                               \
     WG(1, 4, 2, 1) WG(1, 3, 3, 1) WG(1, 2, 3, 1) WG(1, 3, 2, 1) WG(1, 4, 1, 1) WG(1, 2, 2, 1)   \
     WG(1, 3, 1, 1) WG(1, 1, 3, 1) WG(1, 2, 1, 1) WG(1, 1, 2, 1) WG(1, 1, 1, 1)
 
@@ -1461,11 +1461,11 @@ static WgradPlan wgrad_plan_of(const WgTiles &t, int N, int H, int W, int Cin, i
 static WgradPlan wgrad_plan(int N, int H, int W, int Cin, int Cout, int ksize)
 {
     static const WgTiles k3[] = {{2, 1, 4}, {2, 1, 2}, {3, 1, 2}, {1, 1, 4}, {1, 1, 2},
-                                 {2, 1, 1}, {3, 1, 1}, {1, 2, 1}, {1, 1, 1}};
+                                 {2, 1, 1}, {3, 1, 1}, {1, 1, 1}};
     static const WgTiles k1[] = {{4, 2, 1}, {3, 3, 1}, {2, 3, 1}, {3, 2, 1}, {4, 1, 1}, {2, 2, 1},
                                  {3, 1, 1}, {1, 3, 1}, {2, 1, 1}, {1, 2, 1}, {1, 1, 1}};
     const WgTiles *list = ksize == 3 ? k3 : k1;
-    const int n = ksize == 3 ? 9 : 11, TM = (Cout + 15) / 16, TN = (Cin + 15) / 16;
+    const int n = ksize == 3 ? 8 : 11, TM = (Cout + 15) / 16, TN = (Cin + 15) / 16;
     WgradPlan best{};
     size_t most = 0;
     for (int i = 0; i < n; ++i) {

@@ -115,6 +115,17 @@ def test_fbp_general_parts(torch, n, views):
     assert rel_l2(got, O.fbp(g, y)) <= 60 * 3 * 2.5 * 2.0 ** -25
 
 
+def test_fbp_fine_bins_from_the_tile(torch):
+    # The general kernel at 900 bins, with the bound of the other parity tests: offsets from the
+    # tile's centre of 47 bins rms, three roundings of 0.3 * 2^-23 of which, times neighbour
+    # differences of 1.4 of the value, are 4e-6.  (Positions rounded to the detector's 260 bins
+    # rms give five times that.)
+    dect = _dect()
+    g = C.Geometry(**{**RAGGED.__dict__, "n_bins": 900, "bin_mm": 0.2, "n_views": 21})
+    y = f32(P.random_sino(g, 5))
+    assert rel_l2(to_np(dect.fbp(to_dev(torch, y), g)), O.fbp(g, y)) <= 1e-5
+
+
 def test_fbp_pairs_equal_single_calls(torch):
     dect = _dect()
     g = RAGGED

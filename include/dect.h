@@ -342,10 +342,10 @@ typedef struct {
  * height), scaled by the path length per plane; outside the volume is zero.
  * Device buffers: d_vol [nz][ny][nx], d_proj [n_views][n_rows][n_bins]
  * (caller-owned, not aliased).  Uses a library-owned workspace per (device,
- * stream) holding two padded copies of the volume (one for panels of 32 rows
- * and more).  Asynchronous on
- * `stream` except when the view table changes (then the stream is
- * synchronised once).
+ * stream) holding two padded copies of the volume, or one where the rows of
+ * a chunk (of at most 64) are 32 and more, for volumes of up to 64 slices 24
+ * and more (a caller's workspace always holds two).  Asynchronous on `stream`
+ * except when the view table changes (then the stream is synchronised once).
  */
 dect_status dect_cone_project(const dect_cone_geometry *geom, const float *d_vol, float *d_proj,
                               void *stream);
@@ -354,8 +354,9 @@ dect_status dect_cone_project(const dect_cone_geometry *geom, const float *d_vol
  * Cone-beam back-projection d_vol = A3^T d_proj: the transpose of
  * dect_cone_project's matrix in gather form -- every voxel sums over the
  * rays that reach it, with the forward pass's in-plane interpolation weight
- * (the same 32.32 coordinate) and its height weight evaluated in FP64; no
- * atomics, so repeated calls agree bit for bit.  d_vol is overwritten.
+ * (the same 32.32 coordinate) and the weight of its FP64 height, rounded to
+ * FP32 once; no atomics, so repeated calls agree bit for bit.  d_vol is
+ * overwritten.
  * Uses the workspace of dect_cone_project plus a scaled copy of d_proj (for
  * volumes of 20 slices and more one with zero rows around it; a caller's
  * workspace holds the plain copy only).

@@ -19,8 +19,9 @@
 //                view's cos/sin and turned into 32.32 fixed point (in-plane
 //                coordinate and height per plane), stepped by integer adds;
 //                FP32 bilinear samples summed in FP64.
-//   k_cone_pad_z, k_cone_fwd_z : the same with lanes along the rows, for panels
-//                of 32 rows and more, on one padded copy [y][x][z].
+//   k_cone_pad_z, k_cone_fwd_z : the same with lanes along the rows, on one padded
+//                copy [y][x][z]: from 32 rows per chunk, one volume of up to 64
+//                slices from 24 (by lines).
 //   k_cone_tab, k_cone_scale, k_cone_gather : the transpose in gather form
 //                (no atomics, the same result on every run): per-(view, bin)
 //                ray constants, projections times each ray's path length,
@@ -685,7 +686,9 @@ constexpr int kGViews = 64 / kGSlots;
 constexpr int kGMaxRows = 8;      // rows within one voxel of a slice, at most
 // Slices per chunk from which the gather along z is the faster one: it takes
 // 5.6 ms for a chunk of 16 to 64 slices of the size above, k_cone_gather 4.65
-// ms for 16 and 0.29 ms more per slice.
+// ms for 16 and 0.29 ms more per slice.  Small volumes, with fewer blocks than
+// CUs, gain as well: 20 slices of 16^2, 48^2 and 128^2 at 180 views 0.61, 0.55 and
+// 0.60 -> 0.32 ms (16^2 to 192^2 by 20 to 64 slices: 1.3 to 2.7 times).
 constexpr int kGMinSlices = 20;
 constexpr int kGBatch = 4;         // rays whose rows are loaded together
 constexpr int kGStride = 64;      // doubles per column in LDS

@@ -27,7 +27,9 @@ namespace dect {
 namespace {
 
 constexpr int kQPad = 2;           // zero bins on each side of a filtered view
-constexpr int kFbpMaxBins = 6144;  // the filter's taps in LDS (half a double per bin)
+// Bins, at most: the entry point's range (the direct sums grow with the square of the
+// bins; no buffer depends on it).
+constexpr int kFbpMaxBins = 6144;
 
 // The ramp's nonzero taps off the centre have odd distances, so the even bins
 // are filtered from the odd ones and the odd bins from the even ones: two
@@ -37,7 +39,8 @@ constexpr int kFbpMaxBins = 6144;  // the filter's taps in LDS (half a double pe
 // w forms the 16 outputs 2 (m0 + n) + (w & 1), m0 the chunk's first half bin
 // plus 16 (w >> 1).  The weighted rows are staged kFKc bins at a time, the two
 // parities apart (row stride 4 mod 64 dwords: a fragment's 16 rows x 4 bins
-// lie in distinct banks); dynamic LDS holds the taps 1 / (pi^2 (2 i + 1)^2).
+// lie in distinct banks), with the taps 1 / (pi^2 k^2), k odd, between them and
+// the chunk's outputs.
 // 720 rows x 736 bins (390 MFLOP): 19 us alone, 58 us for the direct sums on
 // the vector units (bound by their FP64 conversions and adds); the matrix
 // cores are busy for 5 us of it, the rest is the staging of 16 rows per block

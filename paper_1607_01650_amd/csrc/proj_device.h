@@ -266,17 +266,17 @@ __device__ __forceinline__ void adj_block(AdjShared<NE> &sh, const float *const 
     // are read at once (one per lane), the views that reach the strip taken from
     // the ballot, and their ranges from the lanes.  The order of the sums is that
     // of a walk over every view (an iteration amplifies the rounding of another
-    // order).  The ranges stand in one table over every (strip, view), because the
-    // first view waits for one load then; a list of the reached views alone takes
-    // two that depend on each other (the place in it, then the range): 50 iterations
-    // at 512 x 512, 360 views 8.63 -> 8.48 ms, 30 at 385 x 297, 131 views 2.92 ->
-    // 2.85, 10 of a mixed batch of 16 slices 12.1 -> 11.8.  The ray data of a view's first 64-bin chunk and its lane ranges are
-    // loaded while the previous view is walked: right after a view's first chunk is
-    // staged, the same registers receive the next view's.  These loads are
-    // unconditional (a bin past the range reads the range's last bin, and past the
-    // last view the view before is read again; none of it is used), so the compiler
-    // does not wait for them at a branch.  Further chunks of a view are loaded when
-    // they are reached.
+    // order).  One table holds the ranges of every (strip, view), so the first view
+    // waits for one load; a list of the reached views alone takes two that depend on
+    // each other, the place in it and then the range (50 ADM iterations at 512 x 512,
+    // 360 views: 8.48 ms with the table, 8.63 with the list).
+    //
+    // The ray data of a view's first 64-bin chunk and its lane ranges are loaded
+    // while the previous view is walked: right after a view's first chunk is staged,
+    // the same registers receive the next view's.  These loads are unconditional (a
+    // bin past the range reads the range's last bin, and past the last view the view
+    // before is read again; none of it is used), so the compiler does not wait for
+    // them at a branch.  Further chunks of a view are loaded when they are reached.
     const BinRange *sv = views + (size_t)strip * V;
     const int v_end = (int)((int64_t)V * (g + 1) / nvg);
     int v0 = (int)((int64_t)V * g / nvg) + wid;

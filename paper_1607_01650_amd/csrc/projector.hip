@@ -205,10 +205,10 @@ dect_status launch_fwd(const GeomTables &t, const float *pad2, const float *padT
 
 // View groups per strip: enough blocks to fill the chip (kAdjBlocks), but
 // at least 8 views per group.  A block carries a pair of items.  (Fewer groups
-// write and read fewer partial planes, 128^2 x 60 views 28 against 32 us per ADM
-// iteration, but sum over more views in FP32, which the iteration amplifies:
-// A^T against FP64 at 512^2 x 360 views 2.15e-7 with one group, 1.40e-7 with
-// the four that this gives.)
+// write and read fewer partial planes, 128^2 x 60 views 30.4 against 36.6 us per
+// ADM iteration, but sum over more views in FP32, which the iteration
+// amplifies: A^T against FP64 at 512^2 x 360 views 2.15e-7 with one group,
+// 1.40e-7 with the four that this gives.)
 int adj_groups(const GeomTables &t, int batch)
 {
     const int strips = adj_strips(t.key.nx, t.key.ny);

@@ -672,10 +672,10 @@ __global__ __launch_bounds__(256) void k_cone_scale_z(ConeDev g, const float *__
 // four, a height loses the bits of the distance between rows: A^T's error at
 // rows 20 voxels apart was 1.5e-7, 2.8e-8 now and with k_cone_gather.)
 //
-// Bound by VALU issue: about 25 instructions per (ray, plane) of 64 slices
-// with the window and 33 with the set-up, against 50 to 60 per voxel and view
-// of k_cone_gather, which finds a column's rays and rows again for every 4
-// slices.  512 x 512 x 64, 360 x 64 x 736: 5.6 ms (18.0 ms with k_cone_gather),
+// Bound by VALU issue (88% of it, by the counters): 23 vector, 15 scalar and 3
+// LDS instructions per (ray, plane) of 64 slices, against 50 to 60 vector ones
+// per voxel and view of k_cone_gather, which finds a column's rays and rows again
+// for every 4 slices.  512 x 512 x 64, 360 x 64 x 736: 5.6 ms (18.0 ms with k_cone_gather),
 // 170 cycles per ray and SIMD; a pair on 320 x 289 x 40, 240 x 40 x 460:
 // 2.06 ms (3.94 ms).  Rays in flight (kGBatch): 2, 3, 6 and 8 take 3, 2, 19
 // and 21% longer than 4 (registers against latency).  Eight wavefronts per

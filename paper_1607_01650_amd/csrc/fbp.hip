@@ -41,7 +41,7 @@ constexpr int kFbpMaxBins = 6144;
 // parities apart (row stride 4 mod 64 dwords: a fragment's 16 rows x 4 bins
 // lie in distinct banks), with the taps 1 / (pi^2 k^2), k odd, between them and
 // the chunk's outputs.
-// 720 rows x 736 bins (390 MFLOP): 19 us alone, 58 us for the direct sums on
+// 720 rows x 736 bins (390 MFLOP): 17.5 us traced, 55 for the direct sums on
 // the vector units (bound by their FP64 conversions and adds); the matrix
 // cores are busy for 5 us of it, the rest is the staging of 16 rows per block
 // and the launch.  Staging 768 bins at a time measured the same to 5% slower.
@@ -284,10 +284,12 @@ __global__ __launch_bounds__(256 * S) void k_fbp_bp(const f2v *__restrict__ q,
 // Bound by VALU issue: 14 instructions per pixel and view plus 10 per window.
 // k_fbp_bp's 16-byte load per pixel and view kept the L1 busy (0.94 accesses
 // per cycle) beside 23 VALU instructions.  512 x 512, 360 views, both images: 48
-// us alone (58 us with k_fbp_bp); both kernels of the call 104 -> 60 us, at 128 x 128, 90
-// views 18 -> 13 us.  Error of the metric-size image against FP64 4.9e-6 -> 7e-7.  Tiles of 32 columns (eight pixels per lane) where there
-// are enough of them to fill the chip: 67 against 72 us with 16 columns at the
-// former size; four wavefronts per block instead of eight took 73 us.
+// us traced (55 with k_fbp_bp), the call with its filter 104 -> 60 us; at 128 x
+// 128, 90 views 18 -> 13 us.  The error of that 512 x 512 image against FP64 fell from
+// 4.9e-6 to 7e-7.  Tiles of 32 columns (eight pixels per lane) where there are
+// enough of them to fill the chip: the call took 67 against 72 us with 16 columns
+// at that size when the rule was set; four wavefronts per block instead of eight
+// 73 us.
 constexpr int kBpWin = 64, kBpGroup = 8, kBpWaves = 8;
 constexpr size_t kBpWide = 1024;  // 16 x 16 tiles from which tiles of 32 columns are taken
 

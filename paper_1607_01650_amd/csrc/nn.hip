@@ -306,7 +306,9 @@ __global__ __launch_bounds__(256) void k_conv_fwd(const u16 *__restrict__ X,
 // two blocks per CU (matrix cores and LDS are each a third busy): loading the
 // next window behind the products took 8 x 512^2 64 -> 32 from 160 to 130 us
 // and its input gradient (with the mask) from 285 to 170, a second window in
-// flight to 113 and 163; at 5.1 TB/s their bytes take 78 and 131.
+// flight to 113 and 163.  Again in one session, from graphs: 153 without either,
+// 114 with both, 110 with the addresses in steps; with the mask 272, 137 and 136;
+// at 5.1 TB/s their bytes take 78 and 131.
 constexpr int kC3Chunk = 32;
 constexpr int kC3Rows = 8, kC3MT = 4;                // tile rows, rows per wave
 constexpr int kC3HR = kC3Rows + 2, kC3HC = 34;       // the staged window
